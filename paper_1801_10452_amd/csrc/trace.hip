@@ -669,22 +669,24 @@ trace_kernel(TraceParams p)
                 rk::verlet_step(sp, y, vacc, dl, p.integrator == INTEG_VERLET_CORR, sth, cth);
                 have_acc = true;
             } else {
-                rk::rk4_step(sp, y, dl, sth, cth);
+                rk::rk4_step_angles(sp, y, dl, p.eps <= rk::EPS_CHAINED, &sth, &cth);
             }
             ++steps;
+            // a non-finite derivative reaches the wave vector whichever stage it arises in, so the
+            // wave vector alone tells a failed step
             bool fin = true;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) fin = fin && ::isfinite(y[i]);
+            for (int i = 4; i < 8; ++i) fin = fin && ::isfinite(y[i]);
             if (!fin) {
                 status = RAY_NUMERIC;
             } else {
                 reflected = rk::reflect_pole(y);
                 if (reflected) have_acc = false;   // the carried derivative belongs to the old chart
                 // sin and cos of the new theta from those of the old one (the step moves theta
-                // little); after a reflection from scratch
+                // little; RK4 has them already); after a reflection from scratch
                 if (reflected)
                     rt::sincos_small(y[2], &sth, &cth);
-                else
+                else if (INTEG != INTEG_RK4)
                     rk::sincos_shift(th0, s0, c0, y[2], &sth, &cth);
                 if (y[1] < r_stop)
                     status = RAY_HORIZON;
