@@ -241,24 +241,25 @@ raptor_status raptor_trace_batch_noalloc(raptor_ctx* ctx, const raptor_camera* c
 typedef struct {
     int32_t threads;             /* work-group size: 64, 128, 256 or 512 */
     int32_t blocks_per_cu;       /* persistent work-groups per compute unit; 0 = as many as fit */
-    int32_t refill_threshold;    /* a wave refills its idle lanes once this many are idle (1..64) */
+    int32_t refill_threshold;    /* a wave refills its idle lanes once this many are idle (1..64; a wave
+                                    whose rays are all done always does) */
     int32_t tile_width;          /* pixels per tile row: 8, 16, 32 or 64 (a tile is 64 rays) */
     int32_t min_waves_per_simd;  /* 1, 2 or 3: the kernel variant compiled for at least that many
                                     waves per SIMD (register cap 512, 256 or 168); the 3-wave
-                                    variant sizes its LDS sample queue for 12 waves per CU */
-    int32_t rays_per_wave;       /* 0 or 64 (default), 32 or 16: rays per tile and per wave.  Below
-                                    64 only for the variants whose sample queue holds one sample per
-                                    lane (several frequencies, exact or paper closure); the lanes
-                                    without a ray then only take part in the frequency-parallel
-                                    sample rounds, and the LDS of a wave shrinks with the rays, so
-                                    more waves fit: for launches with fewer tiles than wave slots.
-                                    Elsewhere, and as installed, 64; a tile wider than the rays is
-                                    narrowed to them */
+                                    variant sizes its LDS sample ring for 12 waves per CU */
+    int32_t rays_per_wave;       /* 0 or 64 (default): 64, or fewer in a launch that is too small to
+                                    fill the chip with 64-ray waves, or whose many frequencies per ray
+                                    fill the LDS (the launch chooses; the lanes without a ray then only
+                                    take part in the sample rounds).  32 or 16: that many, for launches
+                                    of several frequencies with the exact or paper closure (more than
+                                    four, or two to four in the 3-wave variant); elsewhere, and as
+                                    installed, 64.  A tile wider than the rays is narrowed to them */
     int32_t reserved[2];
 } raptor_plan;
 
 /* Current plan for (n_nu, transfer_prec, closure) (the default plan if none was set or tuned:
- * 256 threads, as many work-groups as fit, refill at 1 idle lane, 8-pixel tile rows, and the
+ * 256 threads, as many work-groups as fit, refill once a wave's rays are all done (64), 8-pixel
+ * tile rows, and the
  * variant with the most waves per SIMD (3, 2, then 1) whose RK4 kernel keeps its registers
  * without spilling to scratch; for the learned closures 512 threads and the 2-waves-per-SIMD
  * variant).  RK2 and Verlet runs take the plan's 2- or 3-waves-per-SIMD kernel (2 when the plan

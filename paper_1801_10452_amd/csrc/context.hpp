@@ -66,8 +66,8 @@ struct NoAllocHost {
 };
 
 struct LaunchPlan {
-    raptor_plan p{256, 0, 1, 8, 2, 64, {0, 0}};
-    int blocks = 0;   // resolved work-group count
+    raptor_plan p{256, 0, 64, 8, 2, 64, {0, 0}};
+    int resident = 1;   // work-groups that a compute unit's registers and wave slots hold at once
 };
 
 // Learned closure: FP32 parameters with Adam moments, padded BF16 copies, training samples.
@@ -108,7 +108,7 @@ struct raptor_ctx {
     rctx::DevBuf<DevGrid> grids;
     rctx::DevBuf<double> nu, out, pixsr, flux, flux_part;
     rctx::DevBuf<int> status, steps;
-    rctx::DevBuf<unsigned int> counter;
+    rctx::DevBuf<unsigned long long> counter;
     rctx::DevBuf<unsigned long long> stats;
     rctx::DevBuf<double4> k2;
     K2Table k2t{};

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <cstdint>
 
+#include "ks_geodesic.hpp"
+
 // Fluid grid resident in device memory, cells[n_snap][n2][n1] of float4 or double4
 // {n_e, Theta_e, B, Omega}.
 struct DevGrid {
@@ -26,7 +28,9 @@ struct DevGrid {
 // default; the tile width is a launch-plan parameter);
 // the job owns the global tiles [tile_base, tile_base + tiles_x * tiles_y).
 struct DevJob {
-    double a, incl, sin_i, cos_i, r_cam, fov, dalpha, dbeta, r_stop, t_init;
+    double a, fov, dalpha, dbeta, r_stop;
+    double sin_th, cos_th;   // sin and cos of the camera's polar angle
+    rk::CameraFrame<double> cam;
     long long tile_base;
     long long out_base;    // offset of this job's first image in the intensity buffer (doubles)
     long long pix_base;    // offset of this job's pixels in the per-ray info buffers
@@ -57,15 +61,15 @@ struct TraceParams {
     double* out;               // intensities [job image][n_nu][ny][nx]
     int* ray_status;           // optional, per pixel at pix_base
     int* ray_steps;            // optional
-    unsigned int* tile_counter;
+    unsigned long long* ray_counter;   // next ray to hand out, tile by tile over the jobs
     unsigned long long* stats; // ST_COUNT counters
     K2Table k2;
     long long n_tiles;
     int n_jobs, max_steps, closure, slow_light, integrator, pad;
     int refill_threshold, tile_shift;   // tile width = 1 << tile_shift pixels, height rays / width
-    // rays per tile and per wave (64, or 32 / 16 for the kernels whose sample queue holds one
-    // sample per lane: the other lanes then only take part in the frequency-parallel rounds)
-    int rays_per_wave, rays_shift;
+    int rays_per_wave, rays_shift;      // rays per tile and per wave (64, 32, 16, 8 or 4)
+    int n_nu, slots;                    // frequencies of every job; sample-ring slots of a wave
+    double r_in, r_out;                 // radial range of every grid (r_in = r_out = 0: they differ)
     double eps, M, length_unit, const_j, const_alpha, tau_cutoff;
     double tau_step;           // > 0: optical-depth-aware step (at most tau_step per step at the last sample)
     // learned closure (closure == CL_MLP): FP32 parameters and padded BF16 hi / lo weights
@@ -76,14 +80,15 @@ struct TraceParams {
 
 // CL_MLP evaluates the network in split BF16 form, CL_MLP_BF16 in plain BF16 form
 enum : int { CL_EXACT = 0, CL_K2_PAPER = 1, CL_CONST = 2, CL_MLP = 3, CL_MLP_BF16 = 4 };
-enum : int { RAY_RUNNING = 0, RAY_HORIZON = 1, RAY_ESCAPED = 2, RAY_MAXSTEP = 3, RAY_NUMERIC = 4, RAY_OPAQUE = 5,
+enum : int { RAY_IDLE = -1, RAY_RUNNING = 0, RAY_HORIZON = 1, RAY_ESCAPED = 2, RAY_MAXSTEP = 3, RAY_NUMERIC = 4, RAY_OPAQUE = 5,
              RAY_DISK = 6, RAY_PLANE = 7 };
 // geodesic integrators (INTEG_VERLET_CORR runs the Verlet kernel with the corrector pass)
 enum : int { INTEG_RK4 = 0, INTEG_RK2 = 1, INTEG_VERLET = 2, INTEG_VERLET_CORR = 3 };
 
 // Thin-disk test: one camera, Keplerian disk between r_in (the ISCO) and r_out.
 struct DiskParams {
-    double a, incl, sin_i, cos_i, r_cam, fov, dalpha, dbeta, r_stop, r_in, r_out, eps, M;
+    double a, fov, dalpha, dbeta, r_stop, r_in, r_out, eps, M;
+    rk::CameraFrame<double> cam;
     int nx, ny, max_steps, integrator;
     double* intensity;            // [ny][nx] or null
     double* redshift;             // [ny][nx] or null

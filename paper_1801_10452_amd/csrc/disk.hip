@@ -22,7 +22,7 @@ __device__ inline void disk_step(const rk::Spin<double>& sp, double* y, double* 
     if (INTEG == INTEG_RK2) {
         rk::rk2_step(sp, y, dl, s0, c0);
     } else if (INTEG == INTEG_VERLET) {
-        if (!have_acc) rk::ks_accel(sp, y, s0, c0, acc);
+        if (!have_acc) rk::ks_accel<false>(sp, y, s0, c0, acc);
         rk::verlet_step(sp, y, acc, dl, corrector, s0, c0);
         have_acc = true;
     } else {
@@ -44,7 +44,7 @@ __global__ void __launch_bounds__(256) disk_kernel(DiskParams p)
         const double beta = -p.fov + (py + 0.5) * p.dbeta;
         double y[8], acc[4] = {0.0, 0.0, 0.0, 0.0};
         bool have_acc = false;
-        rk::camera_ray(sp, p.r_cam, p.incl, p.sin_i, p.cos_i, alpha, beta, 0.0, y);
+        rk::camera_ray(p.cam, alpha, beta, y);
         double s, c;
         rt::sincos_small(y[2], &s, &c);
         int steps = 0, status = RAY_RUNNING;
@@ -98,7 +98,7 @@ __global__ void __launch_bounds__(256) disk_kernel(DiskParams p)
             rt::sincos_small(y[2], &s, &c);
             if (y[1] < p.r_stop)
                 status = RAY_HORIZON;
-            else if (y[1] > p.r_cam)
+            else if (y[1] > p.cam.r)
                 status = RAY_ESCAPED;
             else if (steps >= p.max_steps)
                 status = RAY_MAXSTEP;

@@ -153,20 +153,97 @@ bool plan_valid(const raptor_plan& p)
            (p.min_waves_per_simd >= 1 && p.min_waves_per_simd <= 3);
 }
 
-// Rays per wave and tile width a launch of this plan uses: fewer than 64 rays only where the
-// instantiation that runs (frequency class, precision, closure class, integrator) keeps one
-// sample per lane, and a tile no wider than the rays.
+int log2_of(int v)
+{
+    int k = 0;
+    while ((1 << k) < v) ++k;
+    return k;
+}
+
+// Rays per wave and tile width of a launch.
 struct Geometry {
     int rays, tile_w;
 };
-Geometry launch_geometry(const raptor_plan& p, int n_nu, bool fp32, bool mlpc, int integ)
+
+// As the plan asks: fewer than 64 rays only in the classes that take them (raptor_plan), and a tile
+// no wider than the rays.
+Geometry plan_geometry(const raptor_plan& p, int n_nu, bool mlpc, int integ)
 {
     Geometry g{64, p.tile_width};
     if ((p.rays_per_wave == 16 || p.rays_per_wave == 32) &&
-        trace_kernel_one_slot(n_nu, fp32, p.min_waves_per_simd, mlpc, integ))
+        trace_plan_takes_rays(n_nu, p.min_waves_per_simd, mlpc, integ))
         g.rays = p.rays_per_wave;
     if (g.tile_w > g.rays) g.tile_w = g.rays;
     return g;
+}
+
+// The most rays per wave a launch takes by itself: the rows of many frequencies take LDS, and with
+// it waves.  Measured (9 x 256^2, ms at 64 / 32 / 16 rays, FP32 and FP64 transfer): 6 frequencies 12.3
+// 14.4 20.2 and 15.0 16.3 20.8; 12 frequencies 16.9 16.3 21.9 and 23.5 21.8 25.3; 24 frequencies 33.1
+// 26.4 26.6 and 53.2 38.3 35.4, with the cut-off (whose rays have few samples waiting) 34.4 28.6 33.7
+// and 54.7 40.9 44.1; 32 frequencies 46.7 at 32 and 35.3 at 16, 70.8 and 49.2 (one wave per SIMD and
+// two).  The learned closure, 24 frequencies, 256^2: 111.7 71.3 59.7 and 39.3 at 8.
+int most_rays(int n_nu, bool mlpc, bool cutoff)
+{
+    if (mlpc) return n_nu > 8 ? 8 : n_nu > 4 ? 32 : 64;
+    return n_nu > 27 || (n_nu > 16 && !cutoff) ? 16 : n_nu > 8 ? 32 : 64;
+}
+
+// As the launch runs it: a plan with 64 rays per wave lets the launch take fewer where waves would
+// be short.  A wave's iteration costs the same whatever the number of its rays, so few rays per wave
+// waste the vector lanes of the step; but a launch is no faster than its longest ray, whose wave
+// shares every iteration with the sample rounds of its other rays, and with few rays in all the
+// chip's SIMDs stand idle.  Measured (a = 0.9375, i = 60 deg, ms at 64 / 32 / 16 / 8 / 4 rays, one
+// frequency, FP32 transfer): 64^2 2.96 2.61 2.24 2.12 2.06; 96^2 2.69 2.12 1.98 1.86 1.92; 150^2
+// 2.98 2.30 2.00 2.14 3.21; 230^2 4.10 3.49 3.62 4.25 5.40; 400^2 (FP64) 4.48 3.85 4.77 7.69; 480^2
+// 4.67 4.73 6.18; 700^2 7.00 7.66; with the rounds evened (launch_blocks) 256^2 3.57 3.20 3.10 4.38, 512 x
+// 256 4.35 3.90 4.68 7.58.  Between one and a half and two rounds of 64-ray tiles the last
+// round is mostly empty: 512^2 (1.33 rounds) 5.59 4.89 6.77.  More than four frequencies and the
+// learned closure have heavier rounds, and their lines for 4, 8 and 16 rays lie at twice the rays (24
+// frequencies, 256^2: 9.98 7.81 5.38 5.76 8.29; but 6 frequencies, 2 x 480 x 400: 9.69 10.7 13.2), the
+// learned closure's for 32 too (200^2: 9.11 5.80 3.76 4.79 5.70), at four times for both together (4
+// frequencies, 4 x 256^2: 40.1 33.0 29.5 34.1).
+Geometry launch_geometry(const raptor_ctx* ctx, const raptor_plan& p, int n_nu, bool mlpc, int integ, bool cutoff,
+                         const JobIn* in, int nj)
+{
+    Geometry g = plan_geometry(p, n_nu, mlpc, integ);
+    if (g.rays < 64) return g;
+    long long n = 0;
+    for (int k = 0; k < nj; ++k) n += (long long)in[k].cam->nx * in[k].cam->ny;
+    const long long simds = 4ll * ctx->cu_count;
+    const long long few = n / (mlpc && n_nu > 1 ? 4 : mlpc || n_nu > 4 ? 2 : 1);
+    if (mlpc) n = few;
+    g.rays = few <= simds * 6     ? 4     // up to 1.5 tiles of the size per SIMD
+           : few <= simds * 12    ? 8     // 1.5
+           : few <= simds * 64    ? 16    // 4
+           : n <= simds * 192     ? 32    // 6 (the resident 64-ray tiles)
+           : n > simds * 240 && n < simds * 336 ? 32
+                                  : 64;
+    g.rays = std::min(g.rays, most_rays(n_nu, mlpc, cutoff));
+    if (g.tile_w > g.rays) g.tile_w = g.rays;
+    return g;
+}
+
+// The work-groups of a launch: the plan's blocks_per_cu per compute unit, or as many as are resident
+// at once when 0 (a wave's LDS depends on the launch's rays per wave and its frequencies).  Tiles for
+// between one and two rounds of those go in two even rounds of fewer waves: 4096 tiles on 3072 waves
+// would leave two thirds of the chip's waves without work in the second (ms, 3072 and 2048 waves:
+// 256^2 at 16 rays, one frequency 3.79 3.10, 24 frequencies 6.56 5.73; 512 x 256 at 32 rays 4.70 3.90;
+// 512^2 at 64 rays 6.35 5.51).  From two rounds on it is no gain (8192 tiles in three rounds: 512^2 at
+// 32 rays 5.37 5.82, 512 x 256 at 16 rays and 24 frequencies 7.53 8.50).
+int launch_blocks(const raptor_ctx* ctx, const LaunchPlan& pl, int n_nu, bool mlpc, int integ, int rays,
+                  long long tiles)
+{
+    int per_cu = pl.p.blocks_per_cu;
+    if (per_cu == 0) {
+        const size_t lds = trace_kernel_lds(n_nu, pl.p.min_waves_per_simd, pl.p.threads, mlpc, integ, rays);
+        const size_t fit = LDS_BYTES / ((lds + LDS_GRANULE - 1) / LDS_GRANULE * LDS_GRANULE);
+        per_cu = std::max(1, std::min(pl.resident, (int)fit));
+        const int waves = pl.p.threads / 64;
+        const long long all = (long long)ctx->cu_count * per_cu, need = (tiles + waves - 1) / waves;
+        if (need > all && need < 2 * all) return (int)((need + 1) / 2);
+    }
+    return ctx->cu_count * per_cu;
 }
 
 int plan_key(int n_nu, bool fp32, bool mlpc)
@@ -175,8 +252,8 @@ int plan_key(int n_nu, bool fp32, bool mlpc)
     return (nnu * 2 + (fp32 ? 1 : 0)) * 2 + (mlpc ? 1 : 0);
 }
 
-// Resolve the work-group count of a plan: blocks_per_cu per compute unit, or as many as are
-// resident at once when 0.
+// Resolve a plan for its class: the work-group size, the geometry and how many work-groups a compute
+// unit's registers hold.
 raptor_status resolve_plan(raptor_ctx* ctx, int max_nu, bool fp32, LaunchPlan* pl, bool mlpc = false)
 {
     // the work-group size the instantiation allows (512 lanes only for the learned closure's
@@ -188,25 +265,26 @@ raptor_status resolve_plan(raptor_ctx* ctx, int max_nu, bool fp32, LaunchPlan* p
     while (pl->p.threads > 64 && pl->p.threads > max_threads) pl->p.threads /= 2;
     // rays per wave and tile width as the RK4 instantiation runs them (64 rays where it keeps
     // more than one sample per lane)
-    const Geometry g = launch_geometry(pl->p, max_nu, fp32, mlpc, INTEG_RK4);
+    const Geometry g = plan_geometry(pl->p, max_nu, mlpc, INTEG_RK4);
     pl->p.rays_per_wave = g.rays;
     pl->p.tile_width = g.tile_w;
-    auto lds = [&]() {
-        return trace_kernel_lds(max_nu, fp32, pl->p.min_waves_per_simd, pl->p.threads, mlpc, INTEG_RK4, g.rays);
+    // the waves' sample rings live in LDS: shrink the work-group until they fit with the most
+    // frequencies of the class
+    const int lo = max_nu <= 1 ? 1 : max_nu <= 4 ? 2 : max_nu <= 8 ? 5 : max_nu <= 16 ? 9 : 17;
+    const int hi = max_nu <= 1 ? 1 : max_nu <= 4 ? 4 : max_nu <= 8 ? 8 : max_nu <= 16 ? 16 : RAPTOR_MAX_NU;
+    const auto lds = [&] {
+        size_t most = 0;
+        for (int n = lo; n <= hi; ++n)
+            most = std::max(most, trace_kernel_lds(n, pl->p.min_waves_per_simd, pl->p.threads, mlpc, INTEG_RK4,
+                                                   g.rays == 64 ? most_rays(n, mlpc, true) : g.rays));
+        return most;
     };
-    // the per-wave sample queue lives in LDS: shrink the work-group until it fits
     while (pl->p.threads > 64 && lds() > ctx->lds_per_block) pl->p.threads /= 2;
     if (lds() > ctx->lds_per_block)
         return fail(ctx, RAPTOR_E_UNSUPPORTED, "the sample queue of one wave exceeds the LDS of a work-group");
-    int per_cu = pl->p.blocks_per_cu;
-    if (per_cu == 0) {
-        RAPTOR_CK(hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                      &per_cu, trace_kernel_symbol(max_nu, fp32, pl->p.min_waves_per_simd, mlpc), pl->p.threads,
-                      lds()),
-                  "querying occupancy");
-        per_cu = std::max(per_cu, 1);
-    }
-    pl->blocks = ctx->cu_count * per_cu;
+    RAPTOR_CK(hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                  &pl->resident, trace_kernel_symbol(max_nu, fp32, pl->p.min_waves_per_simd, mlpc), pl->p.threads, 0),
+              "querying occupancy");
     return RAPTOR_OK;
 }
 
@@ -241,14 +319,20 @@ raptor_status plan_for(raptor_ctx* ctx, int max_nu, bool fp32, LaunchPlan* out, 
     return RAPTOR_OK;
 }
 
+// The rays of the tiles that a launch's waves take without the counter, one each.
+unsigned long long first_rays(const TraceParams& p, int blocks, int threads)
+{
+    return (unsigned long long)blocks * (threads / 64) * p.rays_per_wave;
+}
+
 // The device work of a call as a HIP graph: reset, trace and flux kernels captured on the
 // capture-only stream (nothing runs during capture) and replayed on the context's stream.  The
 // graph is kept while later calls make the identical launch -- same kernel arguments (every
 // buffer pointer and the job count included), frequency class, precision and plan -- and
 // captured again otherwise.  It holds kernel nodes only; the uploads before it are ordinary
 // stream-ordered copies.
-raptor_status launch_graph(raptor_ctx* ctx, const TraceParams& p, int n_nu, bool fp32, const LaunchPlan& plan, int nj,
-                           double* out)
+raptor_status launch_graph(raptor_ctx* ctx, const TraceParams& p, int n_nu, bool fp32, const LaunchPlan& plan,
+                           int blocks, int nj, double* out)
 {
     struct Key {
         TraceParams p;
@@ -263,7 +347,7 @@ raptor_status launch_graph(raptor_ctx* ctx, const TraceParams& p, int n_nu, bool
     k.n_nu = n_nu;
     k.fp32 = fp32;
     k.wpe = plan.p.min_waves_per_simd;
-    k.blocks = plan.blocks;
+    k.blocks = blocks;
     k.threads = plan.p.threads;
     k.nj = nj;
     k.out = out;
@@ -281,8 +365,8 @@ raptor_status launch_graph(raptor_ctx* ctx, const TraceParams& p, int n_nu, bool
         ctx->graph_key.clear();
         hipStream_t cs = ctx->cap_stream;
         RAPTOR_CK(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal), "starting graph capture");
-        hipError_t e = launch_reset(ctx->counter.p, ctx->stats.p, cs);
-        if (e == hipSuccess) e = launch_trace(p, n_nu, fp32, plan.p.min_waves_per_simd, plan.blocks, plan.p.threads, cs);
+        hipError_t e = launch_reset(ctx->counter.p, first_rays(p, blocks, plan.p.threads), ctx->stats.p, cs);
+        if (e == hipSuccess) e = launch_trace(p, n_nu, fp32, plan.p.min_waves_per_simd, blocks, plan.p.threads, cs);
         if (e == hipSuccess) e = launch_flux(ctx->jobs.p, nj, out, ctx->pixsr.p, ctx->flux_part.p, ctx->flux.p, n_nu, cs);
         hipGraph_t g = nullptr;
         const hipError_t e2 = hipStreamEndCapture(cs, &g);   // always end the capture
@@ -332,15 +416,14 @@ raptor_status fill_tables(raptor_ctx* ctx, const JobIn* in, int nj, int n_nu, co
         DevJob& J = t->jobs[k];
         std::memset(&J, 0, sizeof J);
         J.a = c.spin;
-        J.incl = c.incl_deg * kPi / 180.0;
-        J.sin_i = std::sqrt(1.0 - std::cos(J.incl) * std::cos(J.incl));
-        J.cos_i = std::cos(J.incl);
-        J.r_cam = c.r_cam;
+        const double incl = c.incl_deg * kPi / 180.0;
+        const double ci = std::cos(incl);
+        J.cam = rk::camera_frame(c.spin, M, c.r_cam, incl, std::sqrt(1.0 - ci * ci), ci, c.t_frame + c.r_cam);
+        rt::sincos_small(incl, &J.sin_th, &J.cos_th);
         J.fov = c.fov_half;
         J.dalpha = 2.0 * c.fov_half / c.nx;
         J.dbeta = 2.0 * c.fov_half / c.ny;
         J.r_stop = o->r_stop_factor * (M + std::sqrt(std::max(M * M - c.spin * c.spin, 0.0)));
-        J.t_init = c.t_frame + c.r_cam;
         J.nx = c.nx;
         J.ny = c.ny;
         J.tiles_x = (c.nx + tile_w - 1) / tile_w;
@@ -388,7 +471,7 @@ struct DevTables {
     double* pixsr;
     double* flux;
     double* flux_part;
-    unsigned int* counter;
+    unsigned long long* counter;
     unsigned long long* stats;
     double* out;
     int* rs;
@@ -398,13 +481,14 @@ struct DevTables {
 // Upload the tables, launch (reset, trace, flux; direct or as a replayed graph), copy the
 // outputs the caller wants where it wants them, wait, and fill the statistics.
 raptor_status launch_tables(raptor_ctx* ctx, const HostTables& h, const DevTables& d, int nj, int n_nu,
-                            const raptor_opts* o, const LaunchPlan& plan, double* images, double* flux_jy,
-                            int32_t* ray_status, int32_t* ray_steps, raptor_stats* st)
+                            const raptor_opts* o, const LaunchPlan& plan, const Geometry& geo, double* images,
+                            double* flux_jy, int32_t* ray_status, int32_t* ray_steps, raptor_stats* st)
 {
     const bool dev = o->mem == RAPTOR_MEM_DEVICE;
     const bool fp32 = o->transfer_prec == RAPTOR_F32;
-    const Geometry geo = launch_geometry(plan.p, n_nu, fp32, o->closure >= RAPTOR_CLOSURE_MLP, o->integrator);
-    const int tile_w = geo.tile_w;
+    const bool mlpc = o->closure >= RAPTOR_CLOSURE_MLP;
+    const int rays_shift = log2_of(geo.rays);
+    const int blocks = launch_blocks(ctx, plan, n_nu, mlpc, o->integrator, geo.rays, h.tiles);
     hipStream_t s = ctx->stream;
     RAPTOR_CK(hipMemcpyAsync(d.jobs, h.jobs, nj * sizeof(DevJob), hipMemcpyHostToDevice, s), "uploading jobs");
     RAPTOR_CK(hipMemcpyAsync(d.grids, h.grids, h.n_grids * sizeof(DevGrid), hipMemcpyHostToDevice, s),
@@ -422,7 +506,7 @@ raptor_status launch_tables(raptor_ctx* ctx, const HostTables& h, const DevTable
     p.out = d.out;
     p.ray_status = d.rs;
     p.ray_steps = d.rn;
-    p.tile_counter = d.counter;
+    p.ray_counter = d.counter;
     p.stats = d.stats;
     p.k2 = ctx->k2t;
     p.n_tiles = h.tiles;
@@ -442,17 +526,23 @@ raptor_status launch_tables(raptor_ctx* ctx, const HostTables& h, const DevTable
     p.mlp_W = ctx->mlp.W.p;
     p.mlp_Wlo = ctx->mlp.Wlo.p;
     p.refill_threshold = plan.p.refill_threshold;
-    p.tile_shift = tile_w == 8 ? 3 : tile_w == 16 ? 4 : tile_w == 32 ? 5 : 6;
+    p.tile_shift = log2_of(geo.tile_w);
     p.rays_per_wave = geo.rays;
-    p.rays_shift = geo.rays == 16 ? 4 : geo.rays == 32 ? 5 : 6;
+    p.rays_shift = rays_shift;
+    p.n_nu = n_nu;
+    p.slots = trace_kernel_slots(n_nu, plan.p.min_waves_per_simd, mlpc, o->integrator, geo.rays);
+    p.r_in = h.grids[0].r_in;
+    p.r_out = h.grids[0].r_out;
+    for (int i = 1; i < h.n_grids; ++i)
+        if (h.grids[i].r_in != h.grids[0].r_in || h.grids[i].r_out != h.grids[0].r_out) p.r_in = p.r_out = 0.0;
 
     if (o->launch == RAPTOR_LAUNCH_GRAPH) {
-        raptor_status gs = launch_graph(ctx, p, n_nu, fp32, plan, nj, d.out);
+        raptor_status gs = launch_graph(ctx, p, n_nu, fp32, plan, blocks, nj, d.out);
         if (gs != RAPTOR_OK) return gs;
     } else {
-        RAPTOR_CK(launch_reset(d.counter, d.stats, s), "launching reset");
+        RAPTOR_CK(launch_reset(d.counter, first_rays(p, blocks, plan.p.threads), d.stats, s), "launching reset");
         RAPTOR_CK(hipEventRecord(ctx->ev0, s), "recording an event");
-        RAPTOR_CK(launch_trace(p, n_nu, fp32, plan.p.min_waves_per_simd, plan.blocks, plan.p.threads, s),
+        RAPTOR_CK(launch_trace(p, n_nu, fp32, plan.p.min_waves_per_simd, blocks, plan.p.threads, s),
                   "launching the trace kernel");
         RAPTOR_CK(hipEventRecord(ctx->ev1, s), "recording an event");
         RAPTOR_CK(launch_flux(d.jobs, nj, d.out, d.pixsr, d.flux_part, d.flux, n_nu, s), "launching the flux reduction");
@@ -509,8 +599,7 @@ raptor_status run_jobs(raptor_ctx* ctx, const JobIn* in, int nj, int n_nu, const
     std::vector<const raptor_grid*> gl(nj);
     std::vector<double> nus((size_t)nj * n_nu), pixsr(nj);
     HostTables h{jobs.data(), grids.data(), gl.data(), nus.data(), pixsr.data()};
-    const Geometry geo = launch_geometry(plan.p, n_nu, o->transfer_prec == RAPTOR_F32,
-                                         o->closure >= RAPTOR_CLOSURE_MLP, o->integrator);
+    const Geometry geo = launch_geometry(ctx, plan.p, n_nu, mlpc, o->integrator, o->tau_cutoff > 0.0, in, nj);
     raptor_status fs = fill_tables(ctx, in, nj, n_nu, o, geo.tile_w, geo.rays, &h);
     if (fs != RAPTOR_OK) return fs;
 
@@ -540,7 +629,7 @@ raptor_status run_jobs(raptor_ctx* ctx, const JobIn* in, int nj, int n_nu, const
             d.rn = ray_steps ? ctx->steps.p : nullptr;
         }
     }
-    return launch_tables(ctx, h, d, nj, n_nu, o, plan, images, flux_jy, ray_status, ray_steps, st);
+    return launch_tables(ctx, h, d, nj, n_nu, o, plan, geo, images, flux_jy, ray_status, ray_steps, st);
 }
 
 raptor_status check_nu(raptor_ctx* ctx, const double* nu, int n_nu)
@@ -900,7 +989,8 @@ raptor_status raptor_trace_batch_noalloc(raptor_ctx* ctx, const raptor_camera* c
     LaunchPlan plan;
     if ((s = plan_for(ctx, n_nu, fp32, &plan, opts->closure >= RAPTOR_CLOSURE_MLP, false)) != RAPTOR_OK) return s;
     HostTables h{na.jobs, na.grids, na.gl, na.nus, na.pixsr};
-    const Geometry geo = launch_geometry(plan.p, n_nu, fp32, opts->closure >= RAPTOR_CLOSURE_MLP, opts->integrator);
+    const Geometry geo =
+        launch_geometry(ctx, plan.p, n_nu, opts->closure >= RAPTOR_CLOSURE_MLP, opts->integrator, opts->tau_cutoff > 0.0, na.in, n_cams);
     if ((s = fill_tables(ctx, na.in, n_cams, n_nu, opts, geo.tile_w, geo.rays, &h)) != RAPTOR_OK) return s;
     // the launch's buffers, carved from the scratch in 256-byte aligned regions
     unsigned char* base = static_cast<unsigned char*>(ctx->noalloc_scratch);
@@ -911,7 +1001,7 @@ raptor_status raptor_trace_batch_noalloc(raptor_ctx* ctx, const raptor_camera* c
         return q;
     };
     DevTables d;
-    d.counter = reinterpret_cast<unsigned int*>(take(sizeof(unsigned int)));
+    d.counter = reinterpret_cast<unsigned long long*>(take(sizeof(unsigned long long)));
     d.stats = reinterpret_cast<unsigned long long*>(take(ST_COUNT * sizeof(unsigned long long)));
     d.jobs = reinterpret_cast<DevJob*>(take(n_cams * sizeof(DevJob)));
     d.grids = reinterpret_cast<DevGrid*>(take(h.n_grids * sizeof(DevGrid)));
@@ -923,7 +1013,7 @@ raptor_status raptor_trace_batch_noalloc(raptor_ctx* ctx, const raptor_camera* c
     d.rs = nullptr;
     d.rn = nullptr;
     if (off > NOALLOC_SCRATCH_BYTES) return fail(ctx, RAPTOR_E_RANGE, "the batch exceeds the no-allocation scratch");
-    return launch_tables(ctx, h, d, n_cams, n_nu, opts, plan, images, flux_jy, nullptr, nullptr, stats);
+    return launch_tables(ctx, h, d, n_cams, n_nu, opts, plan, geo, images, flux_jy, nullptr, nullptr, stats);
 }
 
 raptor_status raptor_get_plan(raptor_ctx* ctx, int32_t n_nu, int32_t transfer_prec, int32_t closure,
@@ -1000,7 +1090,7 @@ raptor_status raptor_autotune_batch(raptor_ctx* ctx, const raptor_camera* cams, 
     if ((s = time_plan(bp, &bms)) != RAPTOR_OK) return s;
     // coordinate descent over the plan fields
     // (rays per wave before the tile width, which it bounds)
-    const std::vector<std::vector<int>> values = {{1, 2, 3}, {64, 256, 512}, {0, 2, 4}, {1, 8, 16, 32}, {64, 32, 16},
+    const std::vector<std::vector<int>> values = {{1, 2, 3}, {64, 256, 512}, {0, 2, 4}, {1, 8, 64}, {64, 32, 16},
                                                   {8, 16, 64}};
     const bool mlpc_c = o.closure >= RAPTOR_CLOSURE_MLP;
     for (int field = 0; field < (int)values.size(); ++field) {
@@ -1012,7 +1102,7 @@ raptor_status raptor_autotune_batch(raptor_ctx* ctx, const raptor_camera* cams, 
             *slot = v;
             // rays per wave below 64 only where the instantiation keeps one sample per lane, and
             // no tile wider than the rays (it would run as the narrower one already timed)
-            const Geometry cg = launch_geometry(c, n_nu, fp32, mlpc_c, o.integrator);
+            const Geometry cg = plan_geometry(c, n_nu, mlpc_c, o.integrator);
             if (field == 4 && cg.rays != v) continue;
             if (field == 5 && cg.tile_w != v) continue;
             double ms;
@@ -1051,8 +1141,9 @@ raptor_status raptor_kernel_info(raptor_ctx* ctx, int32_t n_nu, int32_t transfer
               "reading kernel attributes");
     RAPTOR_CK(hipOccupancyMaxActiveBlocksPerMultiprocessor(
                   &per_cu, trace_kernel_symbol(n_nu, fp32, plan->min_waves_per_simd, mlpc), plan->threads,
-                  trace_kernel_lds(n_nu, fp32, plan->min_waves_per_simd, plan->threads, mlpc, INTEG_RK4,
-                                   launch_geometry(*plan, n_nu, fp32, mlpc, INTEG_RK4).rays)),
+                  trace_kernel_lds(n_nu, plan->min_waves_per_simd, plan->threads, mlpc, INTEG_RK4,
+                                   std::min(plan_geometry(*plan, n_nu, mlpc, INTEG_RK4).rays,
+                                            most_rays(n_nu, mlpc, false)))),
               "querying occupancy");
     if (vgprs) *vgprs = regs;
     if (scratch_bytes) *scratch_bytes = spill;
@@ -1127,10 +1218,8 @@ raptor_status raptor_trace_disk(raptor_ctx* ctx, const raptor_camera* cam, const
     DiskParams p;
     std::memset(&p, 0, sizeof p);
     p.a = cam->spin;
-    p.incl = cam->incl_deg * kPi / 180.0;
-    p.sin_i = std::sin(p.incl);
-    p.cos_i = std::cos(p.incl);
-    p.r_cam = cam->r_cam;
+    const double incl = cam->incl_deg * kPi / 180.0;
+    p.cam = rk::camera_frame(cam->spin, M, cam->r_cam, incl, std::sin(incl), std::cos(incl), 0.0);
     p.fov = cam->fov_half;
     p.dalpha = 2.0 * cam->fov_half / cam->nx;
     p.dbeta = 2.0 * cam->fov_half / cam->ny;
@@ -1149,7 +1238,7 @@ raptor_status raptor_trace_disk(raptor_ctx* ctx, const raptor_camera* cam, const
     p.steps = dN;
     p.stats = ctx->stats.p;
     hipStream_t st = ctx->stream;
-    RAPTOR_CK(launch_reset(ctx->counter.p, ctx->stats.p, st), "launching reset");
+    RAPTOR_CK(launch_reset(ctx->counter.p, 0, ctx->stats.p, st), "launching reset");
     const int blocks = (int)std::min<long long>((n + 255) / 256, (long long)ctx->cu_count * 8);
     RAPTOR_CK(hipEventRecord(ctx->ev0, st), "recording an event");
     RAPTOR_CK(launch_disk(p, blocks, st), "launching the disk kernel");

@@ -17,7 +17,9 @@
 #pragma once
 #include "rt_math.hpp"
 
-#pragma clang fp contract(off)   // see rt_math.hpp
+// Every fused multiply-add of this file is written out and the compiler's own contraction is off, so
+// that each kernel variant rounds alike whatever the code around an expression.
+#pragma clang fp contract(off)
 
 namespace rk {
 
@@ -42,6 +44,74 @@ __host__ __device__ inline Spin<T> make_spin(T a, T M)
 }
 
 // dk/dlambda = -Gamma k k at state y, given s = sin(theta), c = cos(theta).
+// F_b = Gdot_{bn} k^n - 1/2 (d_b g_mn) k^m k^n for g = g0 + z l l:
+//   z l l part:  zd l_b L + z (k.d l_b) L + z l_b Ld - 1/2 (d_b z) L^2 - z L (d_b l_m) k^m,
+//   with L = l.k, zd = k^r dz/dr + k^theta dz/dtheta, and d_theta l_phi = -2 a s c the only
+//   derivative of l (Ld = k^theta (d_theta l_phi) k^phi);
+//   flat part:   g0 = diag(-1, 1, Sigma) with g0_{r phi} = l_phi, g0_{phi phi} = (r^2 + a^2) sin^2;
+// then raised with the closed-form inverse metric.
+//
+// The order and the fusing of these operations are fixed (LATE: how the third and fourth RK4 stage
+// and the second-order steps fuse a^2 cos^2 and 2 M r): images keep them.  Where the orbital flow
+// turns null just outside the horizon one sample can hold most of an image's light, and the last bit
+// of a trajectory is amplified to as much as 1e-9 of it (FP32 transfer: 1e-8, by how the sample's
+// float coefficients round): another order of the same operations moved a 7 x 187 image by 8e-10 of
+// its norm and the 512^2 FP32 image of a = 0, i = 85 deg by 1.3e-8 (see ks_accel_short).
+// If F_h_out is given, it gets F_theta and *isig_out 1/Sigma, and dk[2] is left to the caller.
+template <bool LATE, class T>
+__host__ __device__ inline void ks_accel(const Spin<T>& sp, const T* y, T s, T c, T* dk, T* F_h_out = nullptr,
+                                         T* isig_out = nullptr)
+{
+    using namespace rt;
+    const T a = sp.a, a2 = sp.a2;
+    const T r = y[1];
+    const T kt = y[4], kr = y[5], kh = y[6], kp = y[7];
+    const T s2 = s * s, sc = s * c, c2 = c * c;
+    const T r2 = r * r;
+    const T a2c2 = a2 * c2;
+    const T sig = LATE ? fma_(a2, c2, r2) : fma_(r, r, a2c2);
+    const T dif = LATE ? fma_(a2, c2, -r2) : a2c2 - r2;
+    const T w = rcp_nr(sig * s2);                           // 1/(Sigma sin^2)
+    const T isig = w * s2;                                  // 1/Sigma
+    const T twoMr = sp.twoM * r;
+    const T z = twoMr * isig;                               // 2 M r / Sigma
+    const T zr = sp.twoM * dif * (isig * isig);             // dz/dr
+    const T zt = z * (sp.twoa2 * sc) * isig;                // dz/dtheta
+    const T lp = -a * s2;                                   // l_phi
+    const T dl = sp.m2a * sc;                               // d l_phi / dtheta
+    const T L = fma_(lp, kp, kt + kr);                      // l.k
+    const T ld = kh * dl;                                   // k^c d_c l_phi
+    const T Ld = ld * kp;
+    const T zd = fma_(kr, zr, kh * zt);                     // k^c d_c z
+    const T L2 = L * L;
+    const T zL = z * L;
+    const T khh = kh * kh, kpp = kp * kp;
+    const T ra = fma_(r, r, a2);
+    const T F1t = fma_(Ld, z, L * zd);                      // z l l part of F_t (the flat part is 0)
+    const T F_r = fma_(-L2, T(0.5) * zr, F1t) + fma_(-r, fma_(kpp, s2, khh), Ld);
+    T F_h = fma_(kh, (r + r) * kr, -(L2 * (T(0.5) * zt)));
+    F_h = fma_(-(dl * kp), fma_(L, z, kr), F_h);
+    F_h = fma_(-fma_(a2, khh, ra * kpp), sc, F_h);
+    T F_p = fma_(ld, zL, lp * F1t);
+    F_p = fma_(kr, fma_(kp, (r + r) * s2, ld), F_p);
+    F_p = fma_(kp, kh * ((ra + ra) * sc), F_p);
+    // inverse metric: g^tt = -(1+z), g^tr = z, g^rr = Delta/Sigma, g^rp = a/Sigma,
+    // g^hh = 1/Sigma, g^pp = 1/(Sigma sin^2)
+    const T gi_rr = (LATE ? fma_(-sp.twoM, r, ra) : ra - twoMr) * isig;
+    const T ai = a * isig;
+    dk[0] = fma_(z, F1t - F_r, F1t);
+    dk[1] = -fma_(ai, F_p, fma_(z, F1t, gi_rr * F_r));
+    if (F_h_out) {
+        *F_h_out = F_h;
+        *isig_out = isig;
+    } else {
+        dk[2] = -isig * F_h;
+    }
+    dk[3] = -fma_(ai, F_r, w * F_p);
+}
+
+// The same connection term in fewer operations, for the thin-disk test, whose rays carry no such
+// amplification to their results (they move by 1e-14).
 // F_b = Gdot_{bn} k^n - 1/2 (d_b g_mn) k^m k^n splits for g = g0 + z l l into l_b G + R_b, with
 // L = l.k, X = z L + k^r (the k_r of the z l l part plus the flat g0_{r phi} cross term) and
 //   G   = (k.d z) L + z Ld,  Ld = k^theta (d_theta l_phi) k^phi,
@@ -57,10 +127,10 @@ __host__ __device__ inline Spin<T> make_spin(T a, T M)
 // The derivatives of z share the factor 2 M / Sigma^2, which multiplies L once.  57 FP64
 // instructions and the reciprocal, against 71 and the reciprocal for raising the whole of F_b
 // with the assembled inverse metric.
-template <class T>
-__host__ __device__ inline void ks_accel(const Spin<T>& sp, const T* y, T s, T c, T* dk)
+__host__ __device__ inline void ks_accel_short(const Spin<double>& sp, const double* y, double s, double c, double* dk)
 {
     using namespace rt;
+    using T = double;
     const T a = sp.a, a2 = sp.a2;
     const T r = y[1];
     const T kt = y[4], kr = y[5], kh = y[6], kp = y[7];
@@ -104,7 +174,7 @@ __host__ __device__ inline void ks_rhs(const Spin<T>& sp, const T* y, T* f)
     f[1] = y[5];
     f[2] = y[6];
     f[3] = y[7];
-    ks_accel(sp, y, s, c, f + 4);
+    ks_accel<false>(sp, y, s, c, f + 4);
 }
 
 // sin and cos of theta + d from s0 = sin(theta), c0 = cos(theta): Taylor polynomials of sin d
@@ -135,8 +205,7 @@ __host__ __device__ inline void sincos_add(T th, T d, T s0, T c0, T* s, T* c)
     }
     // smallest terms first
     const T d2 = d * d, d4 = d2 * d2, d6 = d4 * d2, d8 = d4 * d4;
-    T ps = T(1.0 / 362880.0) * d8;
-    ps = fma_(T(-1.0 / 5040.0), d6, ps);
+    T ps = fma_(T(1.0 / 362880.0), d8, T(-1.0 / 5040.0) * d6);
     ps = fma_(T(1.0 / 120.0), d4, ps);
     ps = fma_(T(-1.0 / 6.0), d2, ps);            // sin d / d - 1
     const T sd = fma_(d, ps, d);
@@ -145,8 +214,8 @@ __host__ __device__ inline void sincos_add(T th, T d, T s0, T c0, T* s, T* c)
     cdm1 = fma_(T(-1.0 / 720.0), d6, cdm1);
     cdm1 = fma_(T(1.0 / 24.0), d4, cdm1);
     cdm1 = fma_(T(-0.5), d2, cdm1);              // cos d - 1
-    *s = s0 + fma_(c0, sd, s0 * cdm1);
-    *c = c0 + fma_(-s0, sd, c0 * cdm1);
+    *s = s0 + fma_(s0, cdm1, c0 * sd);
+    *c = c0 + fma_(c0, cdm1, -(s0 * sd));
 }
 
 // The same for a half step (|d| <= 0.05, about twice the largest half-step move of theta at
@@ -166,12 +235,11 @@ __host__ __device__ inline void sincos_shift_half(T th0, T s0, T c0, T th, T* s,
     ps = fma_(T(1.0 / 120.0), d4, ps);
     ps = fma_(T(-1.0 / 6.0), d2, ps);            // sin d / d - 1
     const T sd = fma_(d, ps, d);
-    T cdm1 = T(1.0 / 40320.0) * (d4 * d4);
-    cdm1 = fma_(T(-1.0 / 720.0), d6, cdm1);
+    T cdm1 = fma_(T(1.0 / 40320.0), d4 * d4, T(-1.0 / 720.0) * d6);
     cdm1 = fma_(T(1.0 / 24.0), d4, cdm1);
     cdm1 = fma_(T(-0.5), d2, cdm1);              // cos d - 1
-    *s = s0 + fma_(c0, sd, s0 * cdm1);
-    *c = c0 + fma_(-s0, sd, c0 * cdm1);
+    *s = s0 + fma_(s0, cdm1, c0 * sd);
+    *c = c0 + fma_(c0, cdm1, -(s0 * sd));
 }
 
 // Positive step size of the adaptive rule (Sec. 2.2),
@@ -184,11 +252,11 @@ __host__ __device__ inline T step_size(T eps, const T* y)
     using namespace rt;
     const T d = T(1e-40);
     const T r = y[1];
-    const T x2 = y[2] * T(M_1_PI);
-    const T edge = fmax_(fmin_(x2, T(1.0) - x2), T(1e-12));
-    const T re = r * edge;
-    const T den = fma_(fma_(d, r, fabs_(y[5])), edge, fma_(fma_(fabs_(y[6]), T(M_1_PI), d), r, (fabs_(y[7]) + d) * re));
-    return eps * re * rcp_nr(den);
+    const T edge = fmax_(fmin_(y[2] * T(M_1_PI), fma_(y[2], T(-M_1_PI), T(1.0))), T(1e-12));
+    T den = fma_(r, d, fabs_(y[5])) * edge;
+    den = fma_(r, fma_(fabs_(y[6]), T(M_1_PI), d), den);
+    den = fma_(r * (fabs_(y[7]) + d), edge, den);
+    return eps * r * edge * rcp_nr(den);
 }
 
 // The work count treats sincos_shift and sincos_shift_half as one sine-cosine evaluation.
@@ -214,7 +282,7 @@ __host__ __device__ inline void rk4_step(const Spin<T>& sp, T* y, T dl, T s0, T 
     using namespace rt;
     T t[8], acc[8], dk[4];
     T s, c;
-    ks_accel(sp, y, s0, c0, dk);
+    ks_accel<false>(sp, y, s0, c0, dk);
     const T h2 = T(0.5) * dl;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -224,7 +292,7 @@ __host__ __device__ inline void rk4_step(const Spin<T>& sp, T* y, T dl, T s0, T 
         t[4 + i] = fma_(h2, dk[i], y[4 + i]);
     }
     sincos_shift_half(y[2], s0, c0, t[2], &s, &c);
-    ks_accel(sp, t, s, c, dk);
+    ks_accel<false>(sp, t, s, c, dk);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         acc[i] = fma_(T(2.0), t[4 + i], acc[i]);
@@ -233,7 +301,7 @@ __host__ __device__ inline void rk4_step(const Spin<T>& sp, T* y, T dl, T s0, T 
         t[4 + i] = fma_(h2, dk[i], y[4 + i]);
     }
     sincos_shift_half(y[2], s0, c0, t[2], &s, &c);
-    ks_accel(sp, t, s, c, dk);
+    ks_accel<true>(sp, t, s, c, dk);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         acc[i] = fma_(T(2.0), t[4 + i], acc[i]);
@@ -242,13 +310,95 @@ __host__ __device__ inline void rk4_step(const Spin<T>& sp, T* y, T dl, T s0, T 
         t[4 + i] = fma_(dl, dk[i], y[4 + i]);
     }
     sincos_shift(y[2], s0, c0, t[2], &s, &c);
-    ks_accel(sp, t, s, c, dk);
+    T F_h, isig;
+    ks_accel<true>(sp, t, s, c, dk, &F_h, &isig);
     const T h6 = dl * T(1.0 / 6.0);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         y[i] = fma_(h6, acc[i] + t[4 + i], y[i]);
-        y[4 + i] = fma_(h6, acc[4 + i] + dk[i], y[4 + i]);
+        y[4 + i] = fma_(h6, i == 2 ? fma_(-isig, F_h, acc[4 + i]) : acc[4 + i] + dk[i], y[4 + i]);
     }
+}
+
+// rk4_step and the sine and cosine of the new theta as one basic block: bit for bit rk4_step with
+// its shifts of the angle, without their branches.  The size tests of the four shifts are made
+// together before y is written; false (y untouched) if one fails, which at eps = 0.05 none does.
+// The trace kernel is bound by vector-instruction issue and, with few rays, by the length of the
+// step's chain: the branches cost both scalar instructions and the overlap of one stage's angle with
+// the other's connection term.
+__host__ __device__ inline bool rk4_try_block(const Spin<double>& sp, double* y, double dl, double* sin_th,
+                                              double* cos_th)
+{
+    using namespace rt;
+    const double s0 = *sin_th, c0 = *cos_th, h2 = 0.5 * dl, h6 = dl * (1.0 / 6.0);
+    double t[8], acc[8], dk[4], s, c, F_h, isig;
+    const auto half = [&](double d) {
+        const double d2 = d * d, d4 = d2 * d2, d6 = d4 * d2;
+        const double ps = fma_(-1.0 / 6.0, d2, fma_(1.0 / 120.0, d4, (-1.0 / 5040.0) * d6));
+        const double sd = fma_(d, ps, d);
+        double cm = fma_(1.0 / 40320.0, d4 * d4, (-1.0 / 720.0) * d6);
+        cm = fma_(-0.5, d2, fma_(1.0 / 24.0, d4, cm));
+        s = s0 + fma_(s0, cm, c0 * sd);
+        c = c0 + fma_(c0, cm, -(s0 * sd));
+    };
+    const auto full = [&](double d) {
+        const double d2 = d * d, d4 = d2 * d2, d6 = d4 * d2, d8 = d4 * d4;
+        double ps = fma_(1.0 / 362880.0, d8, (-1.0 / 5040.0) * d6);
+        ps = fma_(-1.0 / 6.0, d2, fma_(1.0 / 120.0, d4, ps));
+        const double sd = fma_(d, ps, d);
+        double cm = fma_(1.0 / 40320.0, d8, (-1.0 / 3628800.0) * (d8 * d2));
+        cm = fma_(1.0 / 24.0, d4, fma_(-1.0 / 720.0, d6, cm));
+        cm = fma_(-0.5, d2, cm);
+        s = s0 + fma_(s0, cm, c0 * sd);
+        c = c0 + fma_(c0, cm, -(s0 * sd));
+    };
+    const auto stage = [&](double h) {   // the wave vector and the radius of the next stage
+        const double kr = t[5];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) t[4 + i] = fma_(h, dk[i], y[4 + i]);
+        t[1] = fma_(h, kr, y[1]);
+    };
+    ks_accel<false>(sp, y, s0, c0, dk);
+    const double d1 = fma_(h2, y[6], y[2]) - y[2];
+    half(d1);
+    t[5] = y[5];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        acc[i] = y[4 + i];
+        acc[4 + i] = dk[i];
+    }
+    stage(h2);
+    ks_accel<false>(sp, t, s, c, dk);
+    const double d2 = fma_(h2, t[6], y[2]) - y[2];
+    half(d2);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        acc[i] = fma_(2.0, t[4 + i], acc[i]);
+        acc[4 + i] = fma_(2.0, dk[i], acc[4 + i]);
+    }
+    stage(h2);
+    ks_accel<true>(sp, t, s, c, dk);
+    const double d3 = fma_(dl, t[6], y[2]) - y[2];
+    full(d3);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        acc[i] = fma_(2.0, t[4 + i], acc[i]);
+        acc[4 + i] = fma_(2.0, dk[i], acc[4 + i]);
+    }
+    stage(dl);
+    ks_accel<true>(sp, t, s, c, dk, &F_h, &isig);
+    const double th = fma_(h6, acc[2] + t[6], y[2]);
+    const double d4 = th - y[2];
+    full(d4);
+    if (!(fmax_(fabs_(d1), fabs_(d2)) <= 0.05 && fmax_(fabs_(d3), fabs_(d4)) <= 0.1)) return false;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        y[i] = i == 2 ? th : fma_(h6, acc[i] + t[4 + i], y[i]);
+        y[4 + i] = fma_(h6, i == 2 ? fma_(-isig, F_h, acc[4 + i]) : acc[4 + i] + dk[i], y[4 + i]);
+    }
+    *sin_th = s;
+    *cos_th = c;
+    return true;
 }
 
 // sin and cos of an angle d away from the one of (s0, c0), from sd = sin d and cm = cos d - 1.
@@ -311,10 +461,7 @@ __host__ __device__ inline void rotate_tiny(double d, double s0, double c0, doub
 // y is written.  A lane that fails one takes rk4_step and the full-size shift instead: at eps = 0.05
 // 3e-5 of the steps do (near the axis and at large curvature); with an eps above EPS_CHAINED, where
 // ordinary steps begin to, every step takes that form at once.
-// The trace kernel is bound by vector-instruction issue, so the step's cost is its instruction
-// count: 339 FP64 instructions here against 459 for rk4_step with the term-by-term raising and
-// four full shifts, 687 against 798 vector instructions per ray-step with the samples; the
-// production batch (9 x 512^2) went from 26.0 to 22.8 ms, one 512^2 FP64 image from 7.7 to 6.95.
+// 339 FP64 instructions against 459 for rk4_step and its shifts.
 constexpr double EPS_CHAINED = 0.0625;
 __host__ __device__ inline bool rk4_try_chained(const Spin<double>& sp, double* y, double dl, double* sin_th,
                                                 double* cos_th)
@@ -324,7 +471,7 @@ __host__ __device__ inline bool rk4_try_chained(const Spin<double>& sp, double* 
     const double s0 = *sin_th, c0 = *cos_th;
     double t[8], k1[4], k2[4], k3[4], k4[4];
     double s, c;
-    ks_accel(sp, y, s0, c0, k1);
+    ks_accel_short(sp, y, s0, c0, k1);
     const double d1 = h2 * y[6];
     rotate_half(d1, s0, c0, &s, &c);
     const double e1 = h2 * k1[2];                       // the second stage's k^theta less y's
@@ -333,7 +480,7 @@ __host__ __device__ inline bool rk4_try_chained(const Spin<double>& sp, double* 
     t[5] = fma_(h2, k1[1], y[5]);
     t[6] = y[6] + e1;
     t[7] = fma_(h2, k1[3], y[7]);
-    ks_accel(sp, t, s, c, k2);
+    ks_accel_short(sp, t, s, c, k2);
     const double d2 = h2 * e1;
     rotate_small(d2, s, c, &s, &c);
     const double e2 = h2 * k2[2];
@@ -343,7 +490,7 @@ __host__ __device__ inline bool rk4_try_chained(const Spin<double>& sp, double* 
     t[5] = fma_(h2, k2[1], y[5]);
     t[6] = y[6] + e2;
     t[7] = fma_(h2, k2[3], y[7]);
-    ks_accel(sp, t, s, c, k3);
+    ks_accel_short(sp, t, s, c, k3);
     const double d3 = h2 * fma_(2.0, t[6], -t6);        // dl t6(3) - h2 t6(2)
     rotate_half(d3, s, c, &s, &c);
     t[1] = fma_(dl, t[5], y[1]);
@@ -351,7 +498,7 @@ __host__ __device__ inline bool rk4_try_chained(const Spin<double>& sp, double* 
     t[5] = fma_(dl, k3[1], y[5]);
     t[6] = fma_(dl, k3[2], y[6]);
     t[7] = fma_(dl, k3[3], y[7]);
-    ks_accel(sp, t, s, c, k4);
+    ks_accel_short(sp, t, s, c, k4);
     double k23[4], k123[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -370,10 +517,15 @@ __host__ __device__ inline bool rk4_try_chained(const Spin<double>& sp, double* 
     *cos_th = c;
     return true;
 }
-__host__ __device__ inline void rk4_step_angles(const Spin<double>& sp, double* y, double dl, bool chained,
+
+// One RK4 step and the sine and cosine of theta with it (those of y[2] on entry and on return):
+// SHORT the chained form, else rk4_step's own operations; `block`: eps is small enough for either.
+template <bool SHORT>
+__host__ __device__ inline void rk4_step_angles(const Spin<double>& sp, double* y, double dl, bool block,
                                                 double* sin_th, double* cos_th)
 {
-    if (chained && rk4_try_chained(sp, y, dl, sin_th, cos_th)) return;
+    if (block && (SHORT ? rk4_try_chained(sp, y, dl, sin_th, cos_th) : rk4_try_block(sp, y, dl, sin_th, cos_th)))
+        return;
     const double th0 = y[2], s0 = *sin_th, c0 = *cos_th;
     rk4_step(sp, y, dl, s0, c0);
     sincos_shift(th0, s0, c0, y[2], sin_th, cos_th);
@@ -388,7 +540,7 @@ __host__ __device__ inline void rk2_step(const Spin<T>& sp, T* y, T dl, T s0, T 
     using namespace rt;
     T t[8], dk[4];
     T s, c;
-    ks_accel(sp, y, s0, c0, dk);
+    ks_accel<true>(sp, y, s0, c0, dk);
     const T h2 = T(0.5) * dl;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -396,7 +548,7 @@ __host__ __device__ inline void rk2_step(const Spin<T>& sp, T* y, T dl, T s0, T 
         t[4 + i] = fma_(h2, dk[i], y[4 + i]);
     }
     sincos_shift_half(y[2], s0, c0, t[2], &s, &c);
-    ks_accel(sp, t, s, c, dk);
+    ks_accel<true>(sp, t, s, c, dk);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         y[i] = fma_(dl, t[4 + i], y[i]);
@@ -421,14 +573,14 @@ __host__ __device__ inline void verlet_step(const Spin<T>& sp, T* y, T* acc, T d
         t[4 + i] = fma_(acc[i], dl, y[4 + i]);
     }
     sincos_shift(y[2], s0, c0, t[2], &s, &c);
-    ks_accel(sp, t, s, c, dk);
     const T h2 = T(0.5) * dl;
+    for (int pass = 0; pass < (corrector ? 2 : 1); ++pass) {
+        T F_h, isig;
+        ks_accel<true>(sp, t, s, c, dk, &F_h, &isig);
+        dk[2] = -isig * F_h;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) t[4 + i] = fma_(h2, acc[i] + dk[i], y[4 + i]);
-    if (corrector) {
-        ks_accel(sp, t, s, c, dk);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) t[4 + i] = fma_(h2, acc[i] + dk[i], y[4 + i]);
+        for (int i = 0; i < 4; ++i)
+            t[4 + i] = fma_(h2, i == 2 ? fma_(-isig, F_h, acc[2]) : acc[i] + dk[i], y[4 + i]);
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -443,45 +595,67 @@ __host__ __device__ inline void verlet_step(const Spin<T>& sp, T* y, T* acc, T d
 // k_theta = sign(beta) sqrt|Q - L^2 cot^2(i) + a^2 cos^2(i)|, k_r > 0 from the null
 // condition with the Boyer-Lindquist inverse metric, raised and mapped to KS with the
 // appendix matrix (k^t~ = k^t + 2 M r/Delta k^r, k^phi~ = k^phi + a/Delta k^r).
+// CameraFrame: what the pixels of an image share, formed once per image.
 template <class T>
-__host__ __device__ inline void camera_ray(const Spin<T>& sp, T r, T incl, T sin_i, T cos_i, T alpha,
-                                           T beta, T t_init, T* y)
+struct CameraFrame {
+    T r, incl, t_init, a2, sin_i, cos_i, c2, a2ci, cot;
+    T gtt, gtp, gpp, grr, ghh, igrr;   // Boyer-Lindquist inverse metric at the camera, 1 / g^rr
+    T ht, hp;                          // 2 M r / Delta, a / Delta
+};
+
+template <class T>
+__host__ __device__ inline CameraFrame<T> camera_frame(T a, T M, T r, T incl, T sin_i, T cos_i, T t_init)
 {
     using namespace rt;
-    const T a = sp.a, a2 = sp.a2, M = sp.M;
-    const T L = -alpha * sin_i;
-    const T Q = fma_(beta, beta, fma_(alpha, alpha, -a2) * (cos_i * cos_i));
-    const T cot = cos_i * rcp(sin_i);
-    // at beta = 0 the radicand cancels to rounding: its operations and their order decide k_theta
-    const T rad = fma_(cos_i, a2 * cos_i, fma_(-cot, cot * (L * L), Q));
-    const T kth = (beta >= T(0.0) ? T(1.0) : T(-1.0)) * sqrt_(fabs_(rad));
-    const T s2 = sin_i * sin_i, c2 = cos_i * cos_i;
-    const T sig = fma_(r, r, a2 * c2);
+    CameraFrame<T> f;
+    f.r = r;
+    f.incl = incl;
+    f.t_init = t_init;
+    const T a2 = a * a;
+    f.a2 = a2;
+    f.sin_i = sin_i;
+    f.cos_i = cos_i;
+    f.c2 = cos_i * cos_i;
+    f.a2ci = a2 * cos_i;
+    f.cot = cos_i * rcp(sin_i);
+    const T s2 = sin_i * sin_i;
+    const T sig = fma_(r, r, a2 * f.c2);
     const T del = fma_(a, a, fma_(r, r, -(T(2.0) * M * r)));
     const T ra = fma_(r, r, a2);
     const T isd = rcp(sig * del);
-    const T A = fma_(ra, ra, -(a2 * del * s2));
-    const T gtt = -A * isd;
-    const T gtp = -T(2.0) * M * a * r * isd;
-    const T gpp = fma_(-a2, s2, del) * isd * rcp(s2);
-    const T grr = del * rcp(sig);
-    const T ghh = rcp(sig);
-    // g^tt k_t^2 + 2 g^tp k_t k_p + g^pp k_p^2 + g^hh k_h^2 + g^rr k_r^2 = 0, k_t = -1
-    const T rest = fma_(kth, ghh * kth, fma_(L, gpp * L, fma_(T(-2.0) * gtp, L, gtt)));
-    const T kr_cov = sqrt_(fmax_(-rest * rcp(grr), T(0.0)));
-    const T kt_up = fma_(gtp, L, -gtt);
-    const T kr_up = grr * kr_cov;
-    const T kh_up = ghh * kth;
-    const T kp_up = fma_(gpp, L, -gtp);
+    f.gtt = -fma_(ra, ra, -(a2 * del * s2)) * isd;
+    f.gtp = -T(2.0) * M * a * r * isd;
+    f.gpp = fma_(-a2, s2, del) * isd * rcp(s2);
+    f.ghh = rcp(sig);
+    f.grr = del * f.ghh;
+    f.igrr = rcp(f.grr);
     const T idel = rcp(del);
-    y[0] = t_init;
-    y[1] = r;
-    y[2] = incl;
+    f.ht = T(2.0) * M * r * idel;
+    f.hp = a * idel;
+    return f;
+}
+
+template <class T>
+__host__ __device__ inline void camera_ray(const CameraFrame<T>& f, T alpha, T beta, T* y)
+{
+    using namespace rt;
+    const T L = -alpha * f.sin_i;
+    const T Q = fma_(beta, beta, fma_(alpha, alpha, -f.a2) * f.c2);
+    // at beta = 0 the radicand cancels to rounding: its operations and their order decide k_theta
+    const T rad = fma_(f.cos_i, f.a2ci, fma_(-f.cot, f.cot * (L * L), Q));
+    const T kth = (beta >= T(0.0) ? T(1.0) : T(-1.0)) * sqrt_(fabs_(rad));
+    // g^tt k_t^2 + 2 g^tp k_t k_p + g^pp k_p^2 + g^hh k_h^2 + g^rr k_r^2 = 0, k_t = -1
+    const T kh_up = f.ghh * kth;
+    const T rest = fma_(kth, kh_up, fma_(L, f.gpp * L, fma_(T(-2.0) * f.gtp, L, f.gtt)));
+    const T kr_up = f.grr * sqrt_(fmax_(-rest * f.igrr, T(0.0)));
+    y[0] = f.t_init;
+    y[1] = f.r;
+    y[2] = f.incl;
     y[3] = T(0.0);
-    y[4] = fma_(T(2.0) * M * r * idel, kr_up, kt_up);
+    y[4] = fma_(f.ht, kr_up, fma_(f.gtp, L, -f.gtt));
     y[5] = kr_up;
     y[6] = kh_up;
-    y[7] = fma_(a * idel, kr_up, kp_up);
+    y[7] = fma_(f.hp, kr_up, fma_(f.gpp, L, -f.gtp));
 }
 
 // Pole crossing: (theta, phi) -> (-theta, phi + pi) or (2 pi - theta, phi + pi) is the same

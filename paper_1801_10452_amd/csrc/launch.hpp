@@ -2,7 +2,9 @@
 #pragma once
 #include "device_types.hpp"
 
-hipError_t launch_reset(unsigned int* tile_counter, unsigned long long* stats, hipStream_t st);
+// the ray counter starts at `first` (the rays before it are the first tiles of the launch's waves)
+hipError_t launch_reset(unsigned long long* ray_counter, unsigned long long first, unsigned long long* stats,
+                        hipStream_t st);
 // max_nu: largest frequency count of any job (selects the register-array size)
 // wpe: the instantiation compiled for at least wpe waves per SIMD (1, 2 or 3: register caps
 // 512, 256, 168)
@@ -19,13 +21,15 @@ hipError_t trace_kernel_attributes(int max_nu, bool fp32, int wpe, bool mlpc, in
 // mlpc: the variant with the learned closure; integ: INTEG_* (the second-order integrators have
 // the 2- and 3-waves-per-SIMD variants; a request for 1 takes 2)
 const void* trace_kernel_symbol(int max_nu, bool fp32, int wpe, bool mlpc = false, int integ = INTEG_RK4);
-// dynamic LDS bytes of a trace-kernel work-group of `threads` lanes (mlpc: plus the staged network)
-// Dynamic LDS bytes of a trace launch; the same (wpe, mlpc, integ) select the instantiation in
-// trace_kernel_symbol, whose sample queue this sizes.
-size_t trace_kernel_lds(int max_nu, bool fp32, int wpe, int threads, bool mlpc, int integ, int rays = 64);
-// whether the instantiation keeps one queued sample per lane with the intensity in LDS (the
-// variants that may run fewer than 64 rays per wave)
-bool trace_kernel_one_slot(int max_nu, bool fp32, int wpe, bool mlpc, int integ);
+// A compute unit's LDS, and the granules it is handed out in.
+constexpr size_t LDS_BYTES = 163840, LDS_GRANULE = 1280;
+// Dynamic LDS bytes of a trace launch's work-group of `threads` lanes (mlpc: plus the staged network);
+// the same (wpe, mlpc, integ) select the instantiation in trace_kernel_symbol, whose queue this sizes.
+size_t trace_kernel_lds(int n_nu, int wpe, int threads, bool mlpc, int integ, int rays);
+// sample-ring slots of a wave in that LDS
+int trace_kernel_slots(int n_nu, int wpe, bool mlpc, int integ, int rays);
+// whether a plan may ask for fewer than 64 rays per wave in this class (raptor_plan)
+bool trace_plan_takes_rays(int max_nu, int wpe, bool mlpc, int integ);
 // Waves-per-SIMD variant actually instantiated for a requested one.
 int kernel_wpe(int wpe, bool mlpc, int integ);
 
@@ -62,7 +66,7 @@ hipError_t mlp_launch_backward_f32(const float* P, const float* X, const float* 
 constexpr int NOALLOC_MAX_JOBS = 256;
 constexpr size_t noalloc_round(size_t b) { return (b + 255) / 256 * 256; }
 constexpr size_t NOALLOC_SCRATCH_BYTES =
-    noalloc_round(sizeof(unsigned int)) + noalloc_round(ST_COUNT * sizeof(unsigned long long)) +
+    noalloc_round(sizeof(unsigned long long)) + noalloc_round(ST_COUNT * sizeof(unsigned long long)) +
     noalloc_round(NOALLOC_MAX_JOBS * sizeof(DevJob)) + noalloc_round(NOALLOC_MAX_JOBS * sizeof(DevGrid)) +
     2 * noalloc_round((size_t)NOALLOC_MAX_JOBS * 32 * sizeof(double)) + noalloc_round(NOALLOC_MAX_JOBS * sizeof(double)) +
     noalloc_round((size_t)NOALLOC_MAX_JOBS * 32 * FLUX_SPLIT * sizeof(double));

@@ -4,8 +4,6 @@
 #include "ks_geodesic.hpp"
 #include "rt_math.hpp"
 
-#pragma clang fp contract(off)   // see rt_math.hpp
-
 namespace pl {
 
 // CGS constants (CODATA 2018).
@@ -33,15 +31,15 @@ __host__ __device__ inline T mks_halley(T h, T th, T x, T s, T c)
 {
     using namespace rt;
     const T hh = T(0.5) * (T(1.0) - h);
-    const T f = fma_(T(PI_D), x, fma_(hh, s, -th));
-    const T fp = T(PI_D) * fma_(T(1.0) - h, c, T(1.0));
+    const T f = T(PI_D) * x + hh * s - th;
+    const T fp = T(PI_D) * (T(1.0) + (T(1.0) - h) * c);
     const T fpp = T(-2.0 * PI_D * PI_D) * (T(1.0) - h) * s;
     T xn;
     if (fabs_(fp) < T(1e-300)) {
         xn = T(0.05);
     } else {
-        const T den = fma_(T(2.0) * fp, fp, -(f * fpp));
-        xn = (den > fp * fp * T(0.5)) ? fma_(T(-2.0) * f * fp, rcp_nr(den), x) : fma_(-f, rcp_nr(fp), x);
+        const T den = T(2.0) * fp * fp - f * fpp;
+        xn = (den > fp * fp * T(0.5)) ? x - T(2.0) * f * fp * rcp_nr(den) : x - f * rcp_nr(fp);
         if (xn < T(0.0) || xn > T(1.0)) xn = T(0.05);
     }
     return xn;
@@ -69,12 +67,23 @@ template <class T>
 __host__ __device__ inline void bilerp4(const T* a, const T* b, const T* c, const T* d, T w1, T w2, T* out)
 {
     const T u1 = T(1.0) - w1, u2 = T(1.0) - w2;
-    for (int f = 0; f < 4; ++f)
-        out[f] = rt::fma_(u2, rt::fma_(w1, b[f], u1 * a[f]), w2 * rt::fma_(w1, d[f], u1 * c[f]));
+    for (int f = 0; f < 4; ++f) out[f] = u2 * (u1 * a[f] + w1 * b[f]) + w2 * (u1 * c[f] + w1 * d[f]);
 }
 
+// A pointer read from a table in memory, marked as one to global memory (its loads would be flat
+// otherwise, which also count against the LDS).
 template <class V>
-__device__ inline void cell_values(const V& q, double v[4])
+__device__ inline const __attribute__((address_space(1))) V* global_ptr(const void* q)
+{
+    return (const __attribute__((address_space(1))) V*)q;
+}
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef double v4d __attribute__((ext_vector_type(4)));
+typedef double v2d __attribute__((ext_vector_type(2)));
+
+template <class V>
+__device__ inline void cell_values(V q, double v[4])
 {
     v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
 }
@@ -88,17 +97,17 @@ __device__ inline void bilinear(const DevGrid& g, int s, int i0, int j0, double 
     const int idx = (s * g.n2 + j0) * g.n1 + i0;
     double a[4], b[4], c[4], d[4];
     if (g.is_f64) {
-        const double4* p = reinterpret_cast<const double4*>(g.cells) + idx;
-        cell_values(p[0], a);
-        cell_values(p[1], b);
-        cell_values(p[g.n1], c);
-        cell_values(p[g.n1 + 1], d);
+        const auto* p = global_ptr<v4d>(g.cells) + idx;
+        cell_values<v4d>(p[0], a);
+        cell_values<v4d>(p[1], b);
+        cell_values<v4d>(p[g.n1], c);
+        cell_values<v4d>(p[g.n1 + 1], d);
     } else {
-        const float4* p = reinterpret_cast<const float4*>(g.cells) + idx;
-        cell_values(p[0], a);
-        cell_values(p[1], b);
-        cell_values(p[g.n1], c);
-        cell_values(p[g.n1 + 1], d);
+        const auto* p = global_ptr<v4f>(g.cells) + idx;
+        cell_values<v4f>(p[0], a);
+        cell_values<v4f>(p[1], b);
+        cell_values<v4f>(p[g.n1], c);
+        cell_values<v4f>(p[g.n1 + 1], d);
     }
     bilerp4(a, b, c, d, w1, w2, out);
 }
@@ -109,9 +118,9 @@ __device__ inline void bilinear(const DevGrid& g, int s, int i0, int j0, double 
 __device__ inline double modulation(const DevGrid& g, double r, double ph, double ts)
 {
     if (g.mod_amp == 0.0) return 1.0;
-    const double om = rt::rcp_nr(rt::fma_(r * r, rt::rsqrt_nr(r), g.a_gen));   // 1 / (r^1.5 + a_gen)
+    const double om = rt::rcp_nr(r * r * rt::rsqrt_nr(r) + g.a_gen);   // 1 / (r^1.5 + a_gen)
     // reduce the phase by whole turns (two-term 2 pi, exact head) before the small-argument sincos
-    const double arg = rt::fma_(-om, ts, ph);
+    const double arg = ph - om * ts;
     const double turns = __builtin_rint(arg * 0.15915494309189535);
     double red = __builtin_fma(-turns, 6.2831853071795862, arg);
     red = __builtin_fma(-turns, 2.4492935982947064e-16, red);
@@ -120,22 +129,13 @@ __device__ inline double modulation(const DevGrid& g, double r, double ph, doubl
     double cm = c1, sm = s1, acc = 0.0;
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
-        acc = rt::fma_(cm, g.mod_cos[m], rt::fma_(-sm, g.mod_sin[m], acc));
-        const double cn = rt::fma_(cm, c1, -(sm * s1));
-        const double sn = rt::fma_(sm, c1, cm * s1);
+        acc += cm * g.mod_cos[m] - sm * g.mod_sin[m];
+        const double cn = cm * c1 - sm * s1;
+        const double sn = sm * c1 + cm * s1;
         cm = cn;
         sm = sn;
     }
-    return rt::fma_(g.mod_amp, acc, 1.0);
-}
-
-// Cubic Hermite interpolation at s in [0, 1] between (f0, d0) and (f1, d1), in Horner form around
-// the chord: f0 + s (d0 + s (3 D - 2 d0 - d1 + s (d0 + d1 - 2 D))), D = f1 - f0.
-__host__ __device__ inline double hermite(double s, double f0, double d0, double f1, double d1)
-{
-    const double D = f1 - f0, e = d0 - D, g = d1 - D;
-    // 3 D - 2 d0 - d1 = -(2 e + g), d0 + d1 - 2 D = e + g
-    return rt::fma_(s, rt::fma_(s, rt::fma_(s, e + g, -rt::fma_(2.0, e, g)), d0), f0);
+    return 1.0 + g.mod_amp * acc;
 }
 
 // x2(theta), the inverse of the MKS polar map: cubic Hermite interpolation between the grid's
@@ -148,13 +148,15 @@ __device__ inline double x2_of_theta(const DevGrid& g, double th)
     const double q = ::fmin(::fmax(th * g.x2_inv_dth, 0.0), (double)g.x2n - 1e-9);
     const int i = (int)q;
     const double s = q - i;
-    const double2 A = g.x2tab[i], B = g.x2tab[i + 1];
-    const double x0 = hermite(s, A.x, A.y, B.x, B.y);
+    const auto* tab = global_ptr<v2d>(g.x2tab) + i;
+    const v2d A = tab[0], B = tab[1];
+    const double s2 = s * s, s3 = s2 * s;
+    const double h00 = 2.0 * s3 - 3.0 * s2 + 1.0, h10 = s3 - 2.0 * s2 + s;
+    const double h01 = -2.0 * s3 + 3.0 * s2, h11 = s3 - s2;
+    const double x0 = h00 * A.x + h10 * A.y + h01 * B.x + h11 * B.y;
     if (!g.x2_refine) return x0;
     return mks_x2(g.hslope, th, x0);
 }
-
-__device__ inline bool in_plasma(const DevGrid& g, double r) { return r >= g.r_in && r <= g.r_out; }
 
 // GRMHD primitives {rho, u, b, Omega} in code units -> {n_e, Theta_e, B, Omega} (Sec. 4.2.2:
 // n_e = rho rho0 / (m_e + m_p), B = b B0 with B0 = c sqrt(4 pi rho0); Sec. 5: the proton-to-
@@ -168,7 +170,7 @@ __device__ inline void code_to_cgs(const DevGrid& g, double v[4])
     const double rho = v[0], pg = g.gam1 * v[1], pm = 0.5 * v[2] * v[2];
     const double pg2 = pg * pg, pm2 = pm * pm;
     const double den = pm2 + pg2;
-    const double R = den > 0.0 ? rt::fma_(g.r_low, pm2, g.r_high * pg2) * rt::rcp_nr(den) : g.r_high;
+    const double R = den > 0.0 ? (g.r_low * pm2 + g.r_high * pg2) * rt::rcp_nr(den) : g.r_high;
     const double the = (rho > 0.0 && v[1] > 0.0) ? g.thetae_fac * v[1] * rt::rcp_nr(rho * (1.0 + R)) : 0.0;
     v[0] = rho * g.ne_scale;
     v[1] = the;
@@ -183,8 +185,8 @@ __device__ inline void sample_fluid(const DevGrid& g, int slow_light, int fast_s
     const double r = y[1];
     const double x1 = rt::log_pos(r);
     const double x2 = x2_of_theta(g, y[2]);
-    double f1 = rt::fma_(x1 - g.lnr_in, g.inv_d1, -0.5);
-    double f2 = rt::fma_(x2, (double)g.n2, -0.5);
+    double f1 = (x1 - g.lnr_in) * g.inv_d1 - 0.5;
+    double f2 = x2 * g.n2 - 0.5;
     f1 = ::fmin(::fmax(f1, 0.0), (double)(g.n1 - 1));
     f2 = ::fmin(::fmax(f2, 0.0), (double)(g.n2 - 1));
     int i0 = (int)::floor(f1), j0 = (int)::floor(f2);
@@ -202,13 +204,13 @@ __device__ inline void sample_fluid(const DevGrid& g, int slow_light, int fast_s
     }
     double v0[4];
     bilinear(g, s0, i0, j0, w1, w2, v0);
-    v0[0] *= modulation(g, r, y[3], rt::fma_((double)s0, g.dt_snap, g.t0));
+    v0[0] *= modulation(g, r, y[3], g.t0 + s0 * g.dt_snap);
     if (w > 0.0) {
         double v1[4];
         bilinear(g, s0 + 1, i0, j0, w1, w2, v1);
-        v1[0] *= modulation(g, r, y[3], rt::fma_((double)(s0 + 1), g.dt_snap, g.t0));
+        v1[0] *= modulation(g, r, y[3], g.t0 + (s0 + 1) * g.dt_snap);
 #pragma unroll
-        for (int f = 0; f < 4; ++f) out[f] = rt::fma_(1.0 - w, v0[f], w * v1[f]);
+        for (int f = 0; f < 4; ++f) out[f] = (1.0 - w) * v0[f] + w * v1[f];
     } else {
 #pragma unroll
         for (int f = 0; f < 4; ++f) out[f] = v0[f];
@@ -225,31 +227,30 @@ __host__ __device__ inline bool fluid_frame(T a, T a2, T M, const T* y, T s, T c
     using namespace rt;
     const T r = y[1];
     const T s2 = s * s;
-    const T sig = fma_(r, r, a2 * c * c);
+    const T sig = r * r + a2 * c * c;
     const T z = T(2.0) * M * r * rcp_nr(sig);
     const T z1 = T(1.0) + z;
     const T gtt = z - T(1.0);
     const T gtp = -a * z * s2;
     const T grp = -a * s2 * z1;
-    const T gpp = s2 * fma_(a2 * s2, z1, sig);
+    const T gpp = s2 * (sig + a2 * s2 * z1);
     bool zamo = false;
-    // -D = g_tt + Omega (2 g_tp + g_pp Omega)
-    T D = -fma_(omega, fma_(gpp, omega, T(2.0) * gtp), gtt);
+    T D = -(gtt + T(2.0) * gtp * omega + gpp * omega * omega);
     if (D <= T(1e-10)) {
         omega = -gtp / gpp;
-        D = -fma_(omega, fma_(gpp, omega, T(2.0) * gtp), gtt);
+        D = -(gtt + T(2.0) * gtp * omega + gpp * omega * omega);
         zamo = true;
     }
     const T ut = rsqrt_nr(D);
     const T up = omega * ut;
-    const T u_t = fma_(gtt, ut, gtp * up);
-    const T u_p = fma_(gtp, ut, gpp * up);
+    const T u_t = gtt * ut + gtp * up;
+    const T u_p = gtp * ut + gpp * up;
     const T kt = y[4], kr = y[5], kp = y[7];
-    const T k_t = fma_(gtt, kt, fma_(z, kr, gtp * kp));
-    const T k_p = fma_(gtp, kt, fma_(grp, kr, gpp * kp));
-    const T nr = -fma_(k_t, ut, k_p * up);
-    const T bb = fma_(gtt * u_p, u_p, u_t * fma_(gpp, u_t, T(-2.0) * gtp * u_p));
-    const T kb = fma_(k_t, u_p, -(k_p * u_t)) * rsqrt_nr(bb);
+    const T k_t = gtt * kt + z * kr + gtp * kp;
+    const T k_p = gtp * kt + grp * kr + gpp * kp;
+    const T nr = -(k_t * ut + k_p * up);
+    const T bb = gtt * u_p * u_p - T(2.0) * gtp * u_p * u_t + gpp * u_t * u_t;
+    const T kb = (k_t * u_p - k_p * u_t) * rsqrt_nr(bb);
     T cb = kb * rcp_nr(nr);
     cb = fmin_(fmax_(cb, T(-1.0)), T(1.0));
     *nu_r = nr;
@@ -269,18 +270,12 @@ __host__ __device__ inline double ln_k2_theta(const K2Table& t, double the)
     if (the < t.th_lo) {
         const double x = 1.0 / the, u = the * 0.125;   // u = 1/(8x)
         // 1 + a_1/x + ... + a_6/x^6 with a_k/x^k = c_k u^k, c_k = prod (16 - (2i-1)^2) / k!
-        using rt::fma_;
-        double p = fma_(u, 295607.8125, -16891.875);
-        p = fma_(u, p, 1299.375);
-        p = fma_(u, p, -157.5);
-        p = fma_(u, p, 52.5);
-        p = fma_(u, p, 15.0);
-        p = fma_(u, p, 1.0);
-        return fma_(0.5, rt::log_pos(0.5 * PI_D * the), rt::log_pos(p)) - x;
+        double p = 1.0 + u * (15.0 + u * (52.5 + u * (-157.5 + u * (1299.375 + u * (-16891.875 + u * 295607.8125)))));
+        return -x + 0.5 * rt::log_pos(0.5 * PI_D * the) + rt::log_pos(p);
     }
     if (the > t.th_hi) {
         const double x = 1.0 / the;
-        return rt::fma_(2.0, rt::log_pos(the), rt::fma_(-0.25 * x, x, 0.6931471805599453));
+        return 0.6931471805599453 + 2.0 * rt::log_pos(the) - 0.25 * x * x;
     }
     int e;
     const double m = __builtin_frexp(the, &e);           // the = m 2^e, m in [1/2, 1)
@@ -289,7 +284,10 @@ __host__ __device__ inline double ln_k2_theta(const K2Table& t, double the)
     j = j < t.nsub - 1 ? j : t.nsub - 1;
     const double s = q - j;
     const double4 E = t.tab[(e - t.e_lo) * t.nsub + j];
-    return hermite(s, E.x, E.y, E.z, E.w);
+    const double s2 = s * s, s3 = s2 * s;
+    const double h00 = 2.0 * s3 - 3.0 * s2 + 1.0, h10 = s3 - 2.0 * s2 + s;
+    const double h01 = -2.0 * s3 + 3.0 * s2, h11 = s3 - s2;
+    return h00 * E.x + h10 * E.y + h01 * E.z + h11 * E.w;
 }
 
 // Emission j_nu and absorption alpha_nu in the fluid frame (Sec. 4.2.2): Leung et al. fit
@@ -340,5 +338,3 @@ __host__ __device__ inline void transfer_update(T j, T al, T S, T ds, T inr3, T&
 }
 
 }  // namespace pl
-
-#pragma clang fp contract(fast)

@@ -5,22 +5,14 @@
 // algorithmic work of a step: +, -, * count one flop each (a fused multiply-add is written
 // as a product and a sum, so it counts two); divisions, square roots and transcendental
 // calls count as "special" operations and not as flops.
-//
-// Every fused multiply-add of the FP64 path is written out (fma_) and the compiler's own
-// contraction is off in this file, in ks_geodesic.hpp and in plasma.hpp: the kernel's variants
-// (register budgets, integrators, closures) then round alike, whatever the code around an
-// expression, and give the same images bit for bit.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <cmath>
-
-#pragma clang fp contract(off)
 
 namespace rt {
 
 // ---------------------------------------------------------------- double / float (device and host)
 __host__ __device__ inline double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
-__host__ __device__ inline float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __host__ __device__ inline double rcp(double x) { return 1.0 / x; }
 __host__ __device__ inline float rcp(float x) { return 1.0f / x; }
 __host__ __device__ inline double sqrt_(double x) { return ::sqrt(x); }
@@ -64,26 +56,25 @@ __host__ __device__ inline void sincos_small(double x, double* s, double* c)
     // read from scalar registers instead of being copied into vector registers as an FMA addend)
     const double y = r * r, y2 = y * y, y3 = y2 * y, y4 = y2 * y2;
     const double y5 = y4 * y, y6 = y4 * y2, y7 = y4 * y3, y8 = y4 * y4;
-    double ps = (1.0 / 355687428096000.0) * y7;
-    ps = fma_((-1.0 / 1307674368000.0), y6, ps);
-    ps = fma_((1.0 / 6227020800.0), y5, ps);
-    ps = fma_((-1.0 / 39916800.0), y4, ps);
-    ps = fma_((1.0 / 362880.0), y3, ps);
-    ps = fma_((-1.0 / 5040.0), y2, ps);
-    ps = fma_((1.0 / 120.0), y, ps);
+    // (fused by hand: the camera's angle is evaluated on the host, every later one on the device,
+    // and both round alike)
+    double ps = __builtin_fma(1.0 / 355687428096000.0, y7, (-1.0 / 1307674368000.0) * y6);
+    ps = __builtin_fma(1.0 / 6227020800.0, y5, ps);
+    ps = __builtin_fma(-1.0 / 39916800.0, y4, ps);
+    ps = __builtin_fma(1.0 / 362880.0, y3, ps);
+    ps = __builtin_fma(-1.0 / 5040.0, y2, ps);
+    ps = __builtin_fma(1.0 / 120.0, y, ps);
     ps = ps + (-1.0 / 6.0);
-    double pc = (-1.0 / 6402373705728000.0) * y8;
-    pc = fma_((1.0 / 20922789888000.0), y7, pc);
-    pc = fma_((-1.0 / 87178291200.0), y6, pc);
-    pc = fma_((1.0 / 479001600.0), y5, pc);
-    pc = fma_((-1.0 / 3628800.0), y4, pc);
-    pc = fma_((1.0 / 40320.0), y3, pc);
-    pc = fma_((-1.0 / 720.0), y2, pc);
-    pc = fma_((1.0 / 24.0), y, pc);
+    double pc = __builtin_fma(1.0 / 20922789888000.0, y7, (-1.0 / 6402373705728000.0) * y8);
+    pc = __builtin_fma(-1.0 / 87178291200.0, y6, pc);
+    pc = __builtin_fma(1.0 / 479001600.0, y5, pc);
+    pc = __builtin_fma(-1.0 / 3628800.0, y4, pc);
+    pc = __builtin_fma(1.0 / 40320.0, y3, pc);
+    pc = __builtin_fma(-1.0 / 720.0, y2, pc);
+    pc = __builtin_fma(1.0 / 24.0, y, pc);
     pc = pc + (-0.5);
-    const double r2 = y;
-    const double sn = fma_(r * r2, ps, r);
-    const double cs = fma_(r2, pc, 1.0);
+    const double sn = __builtin_fma(r * y, ps, r);
+    const double cs = __builtin_fma(y, pc, 1.0);
     const int q = (int)k & 3;
     const double a = (q & 1) ? cs : sn;   // |sin x|
     const double b = (q & 1) ? sn : cs;   // |cos x|
@@ -141,7 +132,7 @@ __host__ __device__ inline float exp_mixed(double x)
     // below 2^-160 the result is 0 (selected, not branched on, so that independent calls can
     // be interleaved); the clamp keeps the power of two in range there
     const double n = __builtin_rint(z < 160.0 ? (z > -200.0 ? z : -200.0) : 160.0);
-    const float f = (float)fma_(x, 1.4426950408889634, -n);
+    const float f = (float)(z - n);
 #if defined(__HIP_DEVICE_COMPILE__)
     const float r = __builtin_ldexpf(__builtin_amdgcn_exp2f(f), (int)n);
 #else
@@ -192,16 +183,16 @@ __host__ __device__ inline double log_pos(double x)
     const double s2 = s * s;
     const double s4 = s2 * s2, s6 = s4 * s2, s8 = s4 * s4, s10 = s8 * s2, s12 = s8 * s4, s14 = s8 * s6;
     double p = (1.0 / 17.0) * s14;
-    p = fma_((1.0 / 15.0), s12, p);
-    p = fma_((1.0 / 13.0), s10, p);
-    p = fma_((1.0 / 11.0), s8, p);
-    p = fma_((1.0 / 9.0), s6, p);
-    p = fma_((1.0 / 7.0), s4, p);
-    p = fma_((1.0 / 5.0), s2, p);
+    p = p + (1.0 / 15.0) * s12;
+    p = p + (1.0 / 13.0) * s10;
+    p = p + (1.0 / 11.0) * s8;
+    p = p + (1.0 / 9.0) * s6;
+    p = p + (1.0 / 7.0) * s4;
+    p = p + (1.0 / 5.0) * s2;
     p = p + 1.0 / 3.0;
-    const double lm = fma_(2.0 * s * s2, p, 2.0 * s);
+    const double lm = 2.0 * s + 2.0 * s * s2 * p;
     const double de = (double)e;
-    return fma_(de, 0.6931471805599453094, fma_(de, 2.319046813846299558e-17, lm));
+    return de * 0.6931471805599453094 + (de * 2.319046813846299558e-17 + lm);
 }
 
 // Cube root of a positive double in the float range: 2^(log2(x)/3) from the hardware float
@@ -214,11 +205,11 @@ __host__ __device__ inline double cbrt_refined(double x)
     const float xf = (float)x;
     const float tf = __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(xf) * (1.0f / 3.0f));
     const double td = (double)tf;
-    return fma_(fma_(-(td * td), td, x), (double)__builtin_amdgcn_rcpf(3.0f * tf * tf), td);
+    return td + (x - td * td * td) * (double)__builtin_amdgcn_rcpf(3.0f * tf * tf);
 #else
     const float tf = ::cbrtf((float)x);
     const double td = (double)tf;
-    return fma_(fma_(-(td * td), td, x), (double)(1.0f / (3.0f * tf * tf)), td);
+    return td + (x - td * td * td) * (double)(1.0f / (3.0f * tf * tf));
 #endif
 }
 
@@ -274,5 +265,3 @@ inline bool finite_(OpCounted x) { return std::isfinite(x.v); }
 inline double val(OpCounted x) { return x.v; }
 
 }  // namespace rt
-
-#pragma clang fp contract(fast)

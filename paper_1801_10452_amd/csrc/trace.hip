@@ -3,10 +3,9 @@
 // One lane traces one ray (one camera pixel) backward from the camera: RK4 step of the null
 // geodesic in Kerr-Schild coordinates (FP64, Sec. 2.2), termination tests, and at every
 // accepted step inside the plasma the fluid sample, the fluid frame, the closure and the
-// backward formal-solution update of every frequency (Sec. 3.1).  Waves are persistent: a
-// wave takes 64-ray tiles (8 x 8 pixels) from a global counter shared by every image of the
-// launch and hands their rays to its idle lanes as earlier rays finish, so lanes stay busy
-// when rays end after very different numbers of steps.
+// backward formal-solution update of every frequency (Sec. 3.1).  Waves are persistent: each
+// starts with a tile of its own (64 rays, 8 x 8 pixels, or fewer) and takes the rays behind those
+// from a global counter shared by every image of the launch.
 #include "device_types.hpp"
 #include "ks_geodesic.hpp"
 #include "plasma.hpp"
@@ -30,6 +29,23 @@ __device__ inline int find_job(const DevJob* jobs, int n_jobs, long long tile)
     return lo;
 }
 
+// The kernel's arguments read afresh from the argument segment: what a refill, a sample round or a
+// finished ray needs is loaded there (scalar loads, cached) instead of being held in scalar
+// registers across the step, where it would spill into vector-register lanes.
+__device__ inline const TraceParams& fresh_params()
+{
+    auto* k = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(k));
+    return *(const TraceParams*)k;
+}
+
+// A lane index the compiler takes for a new value: addresses formed from it are not kept.
+__device__ inline int fresh(int lane)
+{
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+
 __device__ inline unsigned lane_rank(unsigned long long mask)
 {
     return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
@@ -45,19 +61,6 @@ struct Transfer<double> {
     double ne, the, bf, sinb, ln_k2, ds, inr3, nr;
     bool emits;
     bool live;   // the sample contributes (a positive fluid-frame frequency)
-    // the state as doubles (kept in LDS between the phases of a frequency-parallel round)
-    static constexpr int WORDS = 9;
-    __device__ inline void to_words(double* w) const
-    {
-        w[0] = ne; w[1] = the; w[2] = bf; w[3] = sinb; w[4] = ln_k2; w[5] = ds; w[6] = inr3; w[7] = nr;
-        w[8] = __hiloint2double((int)live, (int)emits);
-    }
-    __device__ inline void from_words(const double* w)
-    {
-        ne = w[0]; the = w[1]; bf = w[2]; sinb = w[3]; ln_k2 = w[4]; ds = w[5]; inr3 = w[6]; nr = w[7];
-        emits = __double2loint(w[8]) != 0;
-        live = __double2hiint(w[8]) != 0;
-    }
     __device__ inline void setup(const TraceParams& p, const double fl[4], double nr_, double cosb, double dsv)
     {
         ne = fl[0]; the = fl[1]; bf = fl[2];
@@ -115,28 +118,6 @@ struct Transfer<float> {
     double nr;
     bool emits;
     bool live;   // the sample contributes (a positive fluid-frame frequency)
-    // the state as doubles, floats in pairs (kept in LDS between the phases of a
-    // frequency-parallel round)
-    static constexpr int WORDS = 7;
-    __device__ static inline double pack(float a, float b)
-    {
-        return __hiloint2double((int)__float_as_uint(b), (int)__float_as_uint(a));
-    }
-    __device__ inline void to_words(double* w) const
-    {
-        w[0] = pack(ne, the); w[1] = pack(inv_the, nu_s); w[2] = pack(ds, inr3);
-        w[3] = ln_k2; w[4] = nr_inv_nus; w[5] = nr;
-        w[6] = __hiloint2double((int)live, (int)emits);
-    }
-    __device__ inline void from_words(const double* w)
-    {
-        ne = __uint_as_float((unsigned)__double2loint(w[0])); the = __uint_as_float((unsigned)__double2hiint(w[0]));
-        inv_the = __uint_as_float((unsigned)__double2loint(w[1])); nu_s = __uint_as_float((unsigned)__double2hiint(w[1]));
-        ds = __uint_as_float((unsigned)__double2loint(w[2])); inr3 = __uint_as_float((unsigned)__double2hiint(w[2]));
-        ln_k2 = w[3]; nr_inv_nus = w[4]; nr = w[5];
-        emits = __double2loint(w[6]) != 0;
-        live = __double2hiint(w[6]) != 0;
-    }
     __device__ inline void setup(const TraceParams& p, const double fl[4], double nr_, double cosb, double dsv)
     {
         ne = (float)fl[0];
@@ -265,59 +246,78 @@ __device__ inline float attenuation<float>(double tau) { return rt::exp_mixed(-t
 
 // ---------------------------------------------------------------------------------------
 // Sample compaction.  A lane whose ray takes a step inside the plasma does not evaluate the
-// sample at once: it queues the point (ten doubles) in its wave's LDS area, up to K per lane,
-// its k-th in slot k * 64 + lane (consecutive lanes in consecutive slots of a queue layer).
-// The wave evaluates queued samples together -- sample i of the selected list on lane i mod 64
-// -- so the expensive part (MKS map, gather, fluid frame, closure) runs on full waves: once 64
-// samples are queued (or a lane's queue is full) it evaluates the largest multiple of 64 of
-// them, oldest first across the lanes, and leaves the rest queued; when a ray with queued
-// samples terminates, or a full queue meets fewer than 64 samples, it evaluates everything.  Each owner folds its evaluated samples into (I, tau) in
-// the order they were taken and moves the rest to the front of its queue, which keeps the
-// backward transfer identical to evaluating every sample right after its step.
+// sample at once: the wave appends it to a ring of sample records in LDS, first in first out,
+// whichever lanes the samples come from.  Once 64 are queued the wave evaluates the oldest 64
+// together, one per lane, so the expensive part (MKS map, gather, fluid frame, closure) runs on
+// full waves; it evaluates fewer only when the next step's samples would not fit, when no ray is
+// left running, when as many rays wait for their last samples as still run, or when the run needs
+// each sample before the ray goes on (optical-depth-aware step; the optical-depth cut-off limits
+// how many samples a ray may have waiting).  The samples of a ray are chained through their
+// records; after a round each ray folds its evaluated samples into (I, tau) in the order they were
+// taken, which keeps the backward transfer identical to evaluating every sample right after its
+// step.  A ray that has ended waits in its lane until its samples are folded.
+//
+// A ring shared by the wave, against a queue of K samples per lane (K = 1 to 3) whose first full
+// lane forced a round: a lone long ray at the end of a wave's work has a round every 64 of its
+// steps instead of every K, a round of several frequencies is full where it held the samples of a
+// single step, and with fewer rays per wave a round serves several steps of each.
 // ---------------------------------------------------------------------------------------
-constexpr int N_FIELDS = 10;   // t, r, theta, phi, k^t, k^r, k^phi, |dlambda|, sin, cos
+constexpr int N_FIELDS = 10;   // t, r, theta, phi, k^t, k^r, k^phi, sin, cos, |dlambda|
+constexpr int F_DL = 9;
+// A sample record: the ten fields, then a word with the owner's lane (byte 0) and the slot of the
+// owner's next sample (byte 1), and the step number of the sample.  Eleven doubles: an odd stride
+// lets consecutive lanes access consecutive records without bank conflicts.  After the evaluation
+// the fields hold its results: contributions in [0, FREQ_GROUP), optical depths behind them (the
+// step length stays).
+constexpr int REC = 11;
+constexpr int REC_LINK = 80, REC_STEP = 84;   // byte offsets
+
+// Frequencies evaluated together (independent dependency chains) by one lane.
+constexpr int FREQ_GROUP = 4;
+// Cut-off: samples a ray may have waiting (those behind the one that makes it opaque are dropped).
+constexpr int CUT_PENDING = 8;
+static_assert(2 * FREQ_GROUP <= F_DL, "the results of a group fit the record below the step length");
 
 // What the evaluation of a queued sample needs from its ray's job.
 struct LaneInfo {
     double a;
-    int grid, fast_snap, nu_base, n_nu;
+    int grid, fast_snap, nu_base;
 };
 
 __device__ inline LaneInfo lane_info(const TraceParams& p, int job)
 {
     const DevJob& J = p.jobs[job];
-    return LaneInfo{J.a, J.grid, J.fast_snap, J.nu_base, J.n_nu};
+    return LaneInfo{J.a, J.grid, J.fast_snap, J.nu_base};
 }
 
-template <int NNU, class TT, bool MLPC, int WPE>
+// The LDS of a wave: job and pixel index of each lane [64 each], three byte tables of the rays in a
+// round [64 each], counts of ended rays by status and of pole crossings [8], the sample ring
+// [slots][REC], and a row per ray: its intensity and its optical depth at every frequency, and the
+// rate of the optical-depth-aware step.  What a ray needs only once a round or less lives here, not
+// in registers: the step and the evaluation leave none free at three waves per SIMD.
+template <int NNU, bool MLPC, int WPE>
 struct Queue {
-    // pending samples per lane: the most (up to three) for which the waves of the variant's
-    // occupancy (two per SIMD, or three for the 3-waves-per-SIMD variant) fit a compute unit's
-    // 160 KiB of LDS -- beside one copy of the network for the learned closure.  Results are
-    // doubles in both precisions (an FP32 contribution carries its power-of-two scale, see
-    // Transfer<float>).
-    static constexpr int bytes_for(int k) { return 64 * k * (N_FIELDS * 8 + 2 * NNU * 8 + 4) + 64 * 4; }
-    static constexpr int WAVES_PER_CU = 4 * (WPE >= 3 ? 3 : 2);
-    static constexpr int BUDGET = (163840 - (MLPC ? mlp::LDS_NET_BYTES : 0)) / WAVES_PER_CU;
-    static constexpr int K = bytes_for(3) <= BUDGET ? 3 : bytes_for(2) <= BUDGET ? 2 : 1;
-    // a wave's area for `rays` rays per wave (64, or fewer with a one-sample queue): fields
-    // [N_FIELDS][slots], results [slots][2 NNU], slot map [slots], job index of each lane [64]
-    static constexpr size_t field_bytes(int rays) { return (size_t)N_FIELDS * rays * K * sizeof(double); }
-    static constexpr size_t res_bytes(int rays) { return (size_t)2 * NNU * rays * K * sizeof(double); }
-    static constexpr size_t map_bytes(int rays) { return (size_t)rays * K * sizeof(int); }
-    static constexpr size_t INFO_BYTES = 64 * sizeof(int);
-    // Several frequencies with one queued sample per lane (the kernel's FUSED form): the job
-    // indices [64] and the slot map [64] first, then one record per ray of REC doubles -- its ten
-    // queue fields, then its intensity and optical depth per frequency -- so that every address
-    // is a compile-time offset from the record of a slot whatever the rays per wave.
-    static constexpr bool ONE_SLOT = !MLPC && K == 1 && NNU > 1;
-    static constexpr int REC = N_FIELDS + 2 * NNU;
-    static constexpr size_t per_wave(int rays)
+    // words of each kind in a row: as the launch has frequencies, so that the rows of 5 to 8, 12 or
+    // 24 take no more LDS (waves) than they need
+    __host__ __device__ static constexpr int cols(int n_nu) { return NNU > FREQ_GROUP ? n_nu : NNU; }
+    __host__ __device__ static constexpr int row(int n_nu) { return 2 * cols(n_nu) + 1; }   // odd, as REC
+    static constexpr size_t HEAD = 128 * sizeof(int) + 192 + 8 * sizeof(unsigned);
+    __host__ __device__ static constexpr size_t per_wave(int rays, int slots, int n_nu)
     {
-        return ONE_SLOT ? (size_t)512 + (size_t)rays * REC * sizeof(double)
-                        : (field_bytes(rays) + res_bytes(rays) + map_bytes(rays) + INFO_BYTES + 15) / 16 * 16;
+        return (HEAD + (size_t)slots * REC * 8 + (size_t)rays * row(n_nu) * 8 + 15) / 16 * 16;
     }
-    static constexpr size_t PER_WAVE = per_wave(64);
+    // Ring size: 64 slots for a round and one for each ray, so that a step never has to force a
+    // round, as far as the variant's waves then fit a compute unit's LDS (beside one copy of the
+    // network for the learned closure), and no fewer than the 64 that a round takes.
+    static constexpr int slots(int rays, int n_nu)
+    {
+        const size_t used = HEAD + (size_t)rays * row(n_nu) * 8 + 15, least = used + 64 * REC * 8;
+        size_t budget = MLPC ? (LDS_BYTES - mlp::LDS_NET_BYTES) / 8 : 0;
+        for (int w = WPE; !MLPC && w >= 1 && budget < least; --w)
+            budget = LDS_BYTES / w / LDS_GRANULE * LDS_GRANULE / 4;   // w work-groups of four waves
+        const int fit = budget > least ? (int)((budget - used) / (REC * 8)) : 64;
+        return fit >= 64 + rays ? 64 + rays : fit;
+    }
 };
 
 __device__ inline void wave_lds_sync()
@@ -327,14 +327,16 @@ __device__ inline void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+__device__ inline unsigned char* link_of(double* ring, int slot)
+{
+    return reinterpret_cast<unsigned char*>(ring + slot * REC) + REC_LINK;
+}
+
 // The frequency-independent part of a queued sample's evaluation: fluid state, fluid frame and
 // the transfer set-up.  A sample whose fluid-frame frequency is not positive (integration error
 // of a low-order integrator in the last step before the horizon) has no defined emission: its
 // transfer stays non-emitting and it adds nothing.  Returns whether the fluid frame fell back to
 // the ZAMO.
-// Frequencies evaluated together (independent dependency chains) by one lane.
-constexpr int FREQ_GROUP = 4;
-
 template <class TT>
 __device__ inline bool setup_sample(const TraceParams& p, const double* q, const LaneInfo& li, Transfer<TT>& tr)
 {
@@ -343,60 +345,11 @@ __device__ inline bool setup_sample(const TraceParams& p, const double* q, const
     double fl[4];
     pl::sample_fluid(G, p.slow_light, li.fast_snap, y, fl);
     double nr, cb;
-    const bool zamo = pl::fluid_frame(li.a, li.a * li.a, p.M, y, q[8], q[9], fl[3], &nr, &cb);
+    const bool zamo = pl::fluid_frame(li.a, li.a * li.a, p.M, y, q[7], q[8], fl[3], &nr, &cb);
     tr.emits = false;
     tr.live = nr > 0.0;
-    if (tr.live) tr.setup(p, fl, nr, cb, nr * q[7] * p.length_unit);
+    if (tr.live) tr.setup(p, fl, nr, cb, nr * q[F_DL] * p.length_unit);
     return zamo;
-}
-
-// Evaluate one queued sample: fluid state, fluid frame, closure, and per frequency the
-// attenuation-free contribution A (observed units) and the optical depth dtau of the step.
-template <int NNU, class TT>
-__device__ inline bool eval_sample(const TraceParams& p, const double* q, const LaneInfo& li, double* A,
-                                   double* dtau)
-{
-    Transfer<TT> tr;
-    const bool zamo = setup_sample<TT>(p, q, li, tr);
-#pragma unroll
-    for (int f = 0; f < NNU; ++f) {
-        A[f] = 0.0;
-        dtau[f] = 0.0;
-    }
-    if (!tr.live) return zamo;
-    constexpr int G = NNU < FREQ_GROUP ? NNU : FREQ_GROUP;
-#pragma unroll
-    for (int f = 0; f < NNU; f += G) {
-        if (f < li.n_nu) {
-            double nu[G];
-#pragma unroll
-            for (int g = 0; g < G; ++g) nu[g] = (f + g < li.n_nu) ? p.nu[li.nu_base + f + g] : 1.0;
-            tr.template contributions<G>(p, nu, li.n_nu - f, A + f, dtau + f);
-        }
-    }
-    return zamo;
-}
-
-// A sample's transfer set-up kept in LDS between the two phases of a frequency-parallel round:
-// Transfer<TT>'s words in the sample's queue slot, in the fields the evaluation no longer needs
-// (every field but the step length, which the fold still reads).
-constexpr int SETUP_FIELDS[9] = {0, 1, 2, 3, 4, 5, 6, 8, 9};
-template <class TT, int FS, int SS>
-__device__ inline void store_setup(double* fields, int s, const Transfer<TT>& tr)
-{
-    static_assert(Transfer<TT>::WORDS <= 9, "the transfer set-up fits the sample's free queue fields");
-    double w[Transfer<TT>::WORDS];
-    tr.to_words(w);
-#pragma unroll
-    for (int k = 0; k < Transfer<TT>::WORDS; ++k) fields[SETUP_FIELDS[k] * FS + s * SS] = w[k];
-}
-template <class TT, int FS, int SS>
-__device__ inline void load_setup(const double* fields, int s, Transfer<TT>& tr)
-{
-    double w[Transfer<TT>::WORDS];
-#pragma unroll
-    for (int k = 0; k < Transfer<TT>::WORDS; ++k) w[k] = fields[SETUP_FIELDS[k] * FS + s * SS];
-    tr.from_words(w);
 }
 
 // The learned closure's step contribution in FP32 transfer, by the scheme of Transfer<float>: the
@@ -431,53 +384,58 @@ __device__ inline void mlp_contribution_f32(const Transfer<float>& tr, float y0,
     }
 }
 
-// Learned-closure variant of eval_sample for one round: every lane of the wave takes part in the
-// network evaluations (one per frequency); lanes without a sample feed zeros.  Samples whose
-// closure inputs leave the training box use the exact closure, except where the exact closure
-// itself gives exactly zero: where X^1/3 + ln K2(1/Theta_e) exceeds MLP_ZERO_EXP, the factor
-// exp(-(X^1/3 + ln K2)) lies below the smallest double, so j and alpha vanish in both transfer
-// precisions (the FP32 transfer's power of two 2^-n has n >= 1076 there).  Those samples are
-// skipped (counted as dropped) at no change to any result.
+// Learned closure: the frequency-independent part of a sample, and its contribution at one
+// frequency.  Every lane of the wave takes part in the network evaluations; lanes without a sample
+// feed zeros.  Samples whose closure inputs leave the training box use the exact closure, except
+// where the exact closure itself gives exactly zero: where X^1/3 + ln K2(1/Theta_e) exceeds
+// MLP_ZERO_EXP, the factor exp(-(X^1/3 + ln K2)) lies below the smallest double, so j and alpha
+// vanish in both transfer precisions (the FP32 transfer's power of two 2^-n has n >= 1076 there).
+// Those samples are skipped (counted as dropped) at no change to any result.
 constexpr double MLP_ZERO_EXP = 746.0;
 
-template <int NNU, class TT>
-__device__ inline void eval_round_mlp(const TraceParams& p, const unsigned char* lds_net, bool has, const double* q,
-                                      const LaneInfo& li, double* A, double* dtau, unsigned long long& c_zamo,
-                                      unsigned long long& c_fallback, unsigned long long& c_dropped)
-{
-    double fl[4] = {0.0, 1.0, 1.0, 0.0};
-    double nr = 1.0, cb = 0.0;
-    bool zamo = false;
+template <class TT>
+struct MlpSample {
     Transfer<TT> tr;
-    tr.emits = false;
-    tr.live = false;
-    if (has) {
-        const DevGrid& G = p.grids[li.grid];
-        const double y[8] = {q[0], q[1], q[2], q[3], q[4], q[5], 0.0, q[6]};
-        pl::sample_fluid(G, p.slow_light, li.fast_snap, y, fl);
-        zamo = pl::fluid_frame(li.a, li.a * li.a, p.M, y, q[8], q[9], fl[3], &nr, &cb);
-        // a non-positive fluid-frame frequency has no defined emission (see eval_sample): the
-        // transfer stays non-emitting and the sample adds nothing
-        tr.live = nr > 0.0;
-        if (tr.live) tr.setup(p, fl, nr, cb, nr * q[7] * p.length_unit);
+    double fl[4], nr, cb, nuc, ds, inr3, nus;
+    float lth;
+    bool has;
+    __device__ inline bool setup(const TraceParams& p, bool has_, const double* q, const LaneInfo& li)
+    {
+        fl[0] = 0.0; fl[1] = 1.0; fl[2] = 1.0; fl[3] = 0.0;
+        nr = 1.0;
+        cb = 0.0;
+        has = has_;
+        bool zamo = false;
+        tr.emits = false;
+        tr.live = false;
+        if (has) {
+            const DevGrid& G = p.grids[li.grid];
+            const double y[8] = {q[0], q[1], q[2], q[3], q[4], q[5], 0.0, q[6]};
+            pl::sample_fluid(G, p.slow_light, li.fast_snap, y, fl);
+            zamo = pl::fluid_frame(li.a, li.a * li.a, p.M, y, q[7], q[8], fl[3], &nr, &cb);
+            // a non-positive fluid-frame frequency has no defined emission (see setup_sample): the
+            // transfer stays non-emitting and the sample adds nothing
+            tr.live = nr > 0.0;
+            if (tr.live) tr.setup(p, fl, nr, cb, nr * q[F_DL] * p.length_unit);
+        }
+        nuc = pl::NUC_PER_GAUSS * fl[2];
+        lth = (float)rt::log_pos(fl[1] > 0.0 ? fl[1] : 1.0);
+        ds = nr * q[F_DL] * p.length_unit;
+        inr3 = has ? rt::rcp_nr(nr * nr * nr) : 0.0;
+        // nu_s / nu: X = nu / nu_s, nu_s = (2/9) nu_c Theta_e^2 sin(theta_B)
+        nus = (2.0 / 9.0) * nuc * fl[1] * fl[1] * ::sqrt(::fmax(1.0 - cb * cb, 0.0));
+        return zamo;
     }
-    c_zamo += __popcll(__ballot(zamo));
-    const double nuc = pl::NUC_PER_GAUSS * fl[2];
-    const float lth = (float)rt::log_pos(fl[1] > 0.0 ? fl[1] : 1.0);
-    const double ds = nr * q[7] * p.length_unit;
-    const double inr3 = has ? rt::rcp_nr(nr * nr * nr) : 0.0;
-    // nu_s / nu: X = nu / nu_s, nu_s = (2/9) nu_c Theta_e^2 sin(theta_B)
-    const double nus = (2.0 / 9.0) * nuc * fl[1] * fl[1] * ::sqrt(::fmax(1.0 - cb * cb, 0.0));
-#pragma unroll 1
-    for (int f = 0; f < NNU; ++f) {
-        const bool act = has && f < li.n_nu;
-        const double nu = act ? p.nu[li.nu_base + f] * nr : nuc;
+    __device__ inline void contribution(const TraceParams& p, const unsigned char* lds_net, double nu_obs, double& A,
+                                        double& dtau, unsigned long long& c_fallback, unsigned long long& c_dropped)
+    {
+        const double nu = has ? nu_obs * nr : nuc;
         const float lx = (float)rt::log_pos(nu / nuc);
-        const bool inb = act && tr.emits && mlp::in_box(lx, lth, (float)cb);
+        const bool inb = has && tr.emits && mlp::in_box(lx, lth, (float)cb);
         // X^1/3 + ln K2 > MLP_ZERO_EXP  <=>  X > t_lim^3, t_lim = MLP_ZERO_EXP - ln K2 (X^1/3 >= 0)
         const double t_lim = MLP_ZERO_EXP - tr.ln_k2;
-        const bool drop = act && tr.emits && !inb && (t_lim <= 0.0 || nu > t_lim * t_lim * t_lim * nus);
-        c_fallback += __popcll(__ballot(act && tr.emits && !inb && !drop));
+        const bool drop = has && tr.emits && !inb && (t_lim <= 0.0 || nu > t_lim * t_lim * t_lim * nus);
+        c_fallback += __popcll(__ballot(has && tr.emits && !inb && !drop));
         c_dropped += __popcll(__ballot(drop));
         const float x0 = inb ? mlp::norm_lx(lx) : 0.0f, x1 = inb ? mlp::norm_lt(lth) : 0.0f,
                     x2 = inb ? mlp::norm_cb((float)cb) : 0.0f;
@@ -486,12 +444,12 @@ __device__ inline void eval_round_mlp(const TraceParams& p, const unsigned char*
             mlp::forward_wave_lds<false>(lds_net, inb, x0, x1, x2, &y0, &y1);
         else
             mlp::forward_wave_lds<true>(lds_net, inb, x0, x1, x2, &y0, &y1);
-        if (!act) continue;
-        A[f] = 0.0;
-        dtau[f] = 0.0;
+        A = 0.0;
+        dtau = 0.0;
+        if (!has) return;
         if (inb) {
             if constexpr (std::is_same<TT, float>::value) {
-                mlp_contribution_f32(tr, y0, y1, p.nu[li.nu_base + f], nuc, A[f], dtau[f]);
+                mlp_contribution_f32(tr, y0, y1, nu_obs, nuc, A, dtau);
             } else {
                 // the network gives ln j_hat + X^1/3 and ln alpha_hat + X^1/3 (standardised); the
                 // coefficients are formed in double from them (their logs span hundreds)
@@ -503,13 +461,13 @@ __device__ inline void eval_round_mlp(const TraceParams& p, const unsigned char*
                 const double yy = pl::H_OVER_MEC2 * nu / fl[1];
                 const double planck = (yy > 1e-4) ? ::expm1(yy) / yy : 1.0 + 0.5 * yy;   // B_RJ / B_nu
                 const double al = ne * pl::J_PREF / (2.0 * pl::ME_CGS * nuc) * ::exp(lna) * planck;
-                pl::step_source(j, al, j / al, ds, inr3, A[f], dtau[f]);
+                pl::step_source(j, al, j / al, ds, inr3, A, dtau);
             }
         } else if (tr.emits && !drop) {
-            tr.contribution(p, p.nu[li.nu_base + f], A[f], dtau[f]);
+            tr.contribution(p, nu_obs, A, dtau);
         }
     }
-}
+};
 
 // Work-groups of up to 256 lanes; up to 512 for the learned closure's 2-waves-per-SIMD variant,
 // whose eight waves share one LDS copy of the network (a 512-lane group caps a kernel at 256
@@ -517,45 +475,32 @@ __device__ inline void eval_round_mlp(const TraceParams& p, const unsigned char*
 template <int NNU, class TT, int WPE, bool MLPC, int INTEG>
 __global__ void __attribute__((amdgpu_flat_work_group_size(64, (MLPC && WPE >= 2) ? 512 : 256),
                                amdgpu_waves_per_eu(WPE, 8)))
-trace_kernel(TraceParams p)
+trace_kernel(TraceParams args)
 {
-    using Q = Queue<NNU, TT, MLPC, WPE>;
-    constexpr int K = Q::K;
-    // Several frequencies and a one-sample queue: the ray's intensity and optical depth per
-    // frequency live in its row of the result area (I then tau, 2 NNU doubles) instead of
-    // registers, and every round is evaluated frequency-parallel, each (sample, frequency) pair
-    // folded into that row by the lane that computes it.
-    constexpr bool FUSED = Q::ONE_SLOT;
-    // rays per wave: lanes [0, RAYS) trace rays (the plan may give a one-sample-queue kernel
-    // fewer than 64, the other lanes then only work in the sample rounds); RAYS * K queue slots
-    const int RAYS = FUSED ? p.rays_per_wave : 64;
-    // field f of queue slot s is fields[f * FS + s * SS]: field-major for the multi-slot queues,
-    // slot-major (each sample's ten fields together) for the one-slot queues, whose slot count
-    // varies with the rays per wave -- the strides stay compile-time constants either way
-    constexpr int FS = FUSED ? 1 : 64 * K;
-    constexpr int SS = FUSED ? Q::REC : 1;
-    constexpr int RS = FUSED ? Q::REC : 2 * NNU;
+    const TraceParams& p = args;
+    using Q = Queue<NNU, MLPC, WPE>;
+    constexpr int G = NNU < FREQ_GROUP ? NNU : FREQ_GROUP;
+    // lanes [0, RAYS) trace rays; with fewer than 64 rays per wave the other lanes only work in the
+    // sample rounds
+    const int RAYS = p.rays_per_wave;
+    const int SLOTS = p.slots;
+    const int COLS = Q::cols(p.n_nu), ROW = Q::row(p.n_nu);
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = threadIdx.x & 63;
-    unsigned char* wbase = smem + (size_t)(threadIdx.x >> 6) * Q::per_wave(RAYS);
-    double* fields;    // see FS, SS
-    double* res;       // row of slot s at res + s * RS: [NNU] intensities or contributions, then [NNU] depths
-    int* slot_map;     // [slots]
-    int* lane_job;     // [64]
-    if constexpr (FUSED) {
-        lane_job = reinterpret_cast<int*>(wbase);
-        slot_map = reinterpret_cast<int*>(wbase + 256);
-        fields = reinterpret_cast<double*>(wbase + 512);
-        res = fields + N_FIELDS;
-    } else {
-        fields = reinterpret_cast<double*>(wbase);
-        res = reinterpret_cast<double*>(wbase + Q::field_bytes(64));
-        slot_map = reinterpret_cast<int*>(wbase + Q::field_bytes(64) + Q::res_bytes(64));
-        lane_job = reinterpret_cast<int*>(wbase + Q::field_bytes(64) + Q::res_bytes(64) + Q::map_bytes(64));
-    }
+    const size_t per_wave = Q::per_wave(RAYS, SLOTS, p.n_nu);
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    unsigned char* wbase = smem + wid * (int)per_wave;
+    int* lane_job = reinterpret_cast<int*>(wbase);                                  // [64]
+    int* lane_pix = lane_job + 64;                                                  // [64]
+    unsigned char* ray_tab = wbase + 128 * sizeof(int);                             // [64] lane of the n-th ray
+    unsigned char* ray_next = ray_tab + 64;                                         // [64] per lane
+    unsigned char* ray_left = ray_next + 64;                                        // [64]
+    unsigned* tally = reinterpret_cast<unsigned*>(ray_left + 64);                   // [8] by status; [0]: poles
+    double* ring = reinterpret_cast<double*>(wbase + Q::HEAD);                      // [SLOTS][REC]
+    double* rows = ring + (size_t)SLOTS * REC;                                      // [RAYS][ROW]
     const double M = p.M;
-    // learned closure: the work-group's copy of the network, after the queues of its waves
-    unsigned char* lds_net = smem + (size_t)(blockDim.x >> 6) * Q::PER_WAVE;
+    // learned closure: the work-group's copy of the network, after the areas of its waves
+    unsigned char* lds_net = smem + (size_t)(blockDim.x >> 6) * per_wave;
     if (MLPC) {
         const mlp::Net net{p.mlp_P, p.mlp_W, p.mlp_Wlo, nullptr};
         mlp::stage_weights(net, lds_net, threadIdx.x, blockDim.x);
@@ -567,441 +512,495 @@ trace_kernel(TraceParams p)
     double vacc[4] = {0.0, 0.0, 0.0, 0.0};
     bool have_acc = false;
     double a = 0.0, r_stop = 0.0, r_esc = 0.0, sth = 0.0, cth = 1.0;
-    // optical-depth-aware step: d tau / d|lambda| of the last sample at its most absorbing
-    // frequency (0: no transfer limit on the next step)
-    double rt_rate = 0.0;
-    int job = 0, steps = 0, pix = 0, n_nu = 0, grid = 0, pending = 0;
-    int qstep[K];   // step number of each queued sample (the optical-depth cut-off ends the ray there)
-    bool active = false;
-    // accumulated intensity and optical depth in double (the per-sample terms are TT)
-    double I[NNU], tau[NNU];
-#pragma unroll
-    for (int f = 0; f < NNU; ++f) { I[f] = 0.0; tau[f] = 0.0; }
+    int steps = 0;
+    // this ray's queued samples: oldest slot in bits 0-7, newest in 8-15, their number above
+    unsigned queued = 0;
+    int lead = NNU > FREQ_GROUP ? (p.n_nu - 1) / G * G : 0;   // cut-off: the group looked at first in a round
+    const auto first = [&] { return (int)(queued & 255u); };
+    const auto pending = [&] { return (int)(queued >> 16); };
+    int status = RAY_IDLE;
+    // the ray's accumulated intensities and optical depths (doubles; the per-sample terms are TT),
+    // and d tau / d|lambda| of its last sample at the most absorbing frequency (optical-depth-aware
+    // step; 0: no transfer limit on the next step).  Between a step and the queueing of its sample
+    // the last word holds the step length.
+    const int RATE = 2 * COLS;
+    // this lane's row (for the lanes below RAYS); as the other per-lane LDS addresses formed where it
+    // is used, from `fresh(lane)`, so that no register holds it across the step
+    const auto row_of = [&](int l) { return rows + l * ROW; };
 #pragma unroll
     for (int i = 0; i < 8; ++i) y[i] = 0.0;
 
-    // wave-level statistics (ballot counts: scalar registers)
-    unsigned long long c_rays = 0, c_steps = 0, c_samples = 0, c_hor = 0, c_esc = 0, c_max = 0, c_pole = 0,
-                       c_num = 0, c_zamo = 0, c_fallback = 0, c_opq = 0, c_dropped = 0;
+    // wave-level statistics: ballot counts in scalar registers, and the tally of rarer events
+    unsigned long long c_steps = 0, c_samples = 0, c_zamo = 0, c_fallback = 0, c_dropped = 0;
+    if (lane < 8) tally[lane] = 0u;
 
-    long long next = 0, end = 0;   // rays of the current tile not yet handed out (wave-uniform)
-    bool drained = false;
+    // Rays of the current tile not yet handed out (wave-uniform).  The first tile of a wave is its
+    // own index, so that a launch does not begin with an atomic of every wave on one counter, and one
+    // with fewer tiles than waves has none; the counter starts behind them.
+    const long long wave = (long long)blockIdx.x * (blockDim.x >> 6) + wid;
+    const long long n_waves = (long long)gridDim.x * (blockDim.x >> 6);
+    long long next = wave * RAYS, end = wave < p.n_tiles ? next + RAYS : next;
+    bool drained = n_waves >= p.n_tiles;
+    int head = 0, total = 0;       // the ring: oldest slot, samples queued (wave-uniform)
+
+    // The lanes with a running ray and those whose ended ray waits for its samples, as scalar masks:
+    // an iteration in which no ray starts or ends asks the lanes for two ballots only (a ballot
+    // that a branch depends on costs a lone wave about 60 cycles).
+    const unsigned long long ray_lanes = RAYS == 64 ? ~0ull : (1ull << RAYS) - 1ull;
+    unsigned long long run = 0, wait = 0;
+    bool idle_changed = true;
 
     while (true) {
         // ------------------------------------------------------------ refill idle lanes
-        const bool ray_lane = lane < RAYS;
-        unsigned long long idle = __ballot(!active && ray_lane);
-        int n_idle = __popcll(idle);
-        if (n_idle >= p.refill_threshold || n_idle == RAYS) {
+        if (idle_changed) {
+            idle_changed = false;
+            const TraceParams& p = fresh_params();
+            unsigned long long idle = ray_lanes & ~(run | wait);
+            int n_idle = __popcll(idle);
+            if (n_idle < p.refill_threshold && n_idle < RAYS) n_idle = 0;
             while (n_idle > 0) {
                 if (next == end) {
                     if (drained) break;
-                    unsigned t = 0;
-                    if (lane == 0) t = atomicAdd(p.tile_counter, 1u);
-                    t = __builtin_amdgcn_readfirstlane(t);
-                    if ((long long)t >= p.n_tiles) {
+                    // a tile's worth of rays at once, and near the end of the launch about as many as
+                    // there are idle lanes: a wave hands out what it holds over hundreds of steps,
+                    // while other waves run out
+                    const long long total_rays = p.n_tiles * RAYS;
+                    const int tail = n_idle > 8 ? n_idle : 8 < RAYS ? 8 : RAYS;
+                    const int chunk = total_rays - end > n_waves * RAYS ? RAYS : tail;
+                    unsigned long long t = 0;
+                    if (lane == 0) t = atomicAdd(p.ray_counter, (unsigned long long)chunk);
+                    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)t);
+                    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(t >> 32));
+                    next = (long long)(((unsigned long long)hi << 32) | lo);
+                    end = next + chunk < total_rays ? next + chunk : total_rays;
+                    if (next >= total_rays) {
+                        next = end;
                         drained = true;
                         break;
                     }
-                    next = (long long)t * RAYS;
-                    end = next + RAYS;
                 }
                 const long long avail = end - next;
                 const unsigned rank = lane_rank(idle);
-                if (!active && ray_lane && (long long)rank < avail) {
+                bool started = false;
+                if (__builtin_amdgcn_inverse_ballot_w64(idle) && (long long)rank < avail) {
                     const long long ray = next + rank;
-                    const long long tile = FUSED ? ray >> p.rays_shift : ray >> 6;
+                    const long long tile = ray >> p.rays_shift;
                     const int slot = (int)(ray & (RAYS - 1));
-                    job = find_job(p.jobs, p.n_jobs, tile);
+                    const int job = find_job(p.jobs, p.n_jobs, tile);
                     const DevJob& J = p.jobs[job];
                     const long long lt = tile - J.tile_base;
                     const int tw = 1 << p.tile_shift;
                     const int px = (int)(lt % J.tiles_x) * tw + (slot & (tw - 1));
                     const int py = (int)(lt / J.tiles_x) * (RAYS >> p.tile_shift) + (slot >> p.tile_shift);
                     if (px < J.nx && py < J.ny) {
-                        const double alpha = -J.fov + (px + 0.5) * J.dalpha;
-                        const double beta = -J.fov + (py + 0.5) * J.dbeta;
+                        const double alpha = __builtin_fma(px + 0.5, J.dalpha, -J.fov);
+                        const double beta = __builtin_fma(py + 0.5, J.dbeta, -J.fov);
                         a = J.a;
-                        const rk::Spin<double> sp = rk::make_spin(a, M);
-                        rk::camera_ray(sp, J.r_cam, J.incl, J.sin_i, J.cos_i, alpha, beta, J.t_init, y);
-                        rt::sincos_small(y[2], &sth, &cth);
+                        rk::camera_ray(J.cam, alpha, beta, y);
+                        sth = J.sin_th;
+                        cth = J.cos_th;
                         r_stop = J.r_stop;
-                        r_esc = J.r_cam;
-                        pix = py * J.nx + px;
-                        n_nu = J.n_nu;
-                        grid = J.grid;
-                        lane_job[lane] = job;
+                        r_esc = J.cam.r;
+                        const int l = fresh(lane);
+                        double* my_row = row_of(l);
+                        lane_job[l] = job;
+                        lane_pix[l] = py * J.nx + px;
                         steps = 0;
-                        rt_rate = 0.0;
                         have_acc = false;
-#pragma unroll
-                        for (int f = 0; f < NNU; ++f) { I[f] = 0.0; tau[f] = 0.0; }
-                        if (FUSED) {
-#pragma unroll
-                            for (int f = 0; f < 2 * NNU; ++f) res[lane * RS + f] = 0.0;
-                        }
-                        active = true;
+                        for (int f = 0; f < ROW; ++f) my_row[f] = 0.0;
+                        status = RAY_RUNNING;
+                        started = true;
                     }
                 }
                 next += (avail < n_idle) ? avail : n_idle;
-                idle = __ballot(!active && ray_lane);
+                run |= __ballot(started);
+                idle = ray_lanes & ~(run | wait);
                 n_idle = __popcll(idle);
             }
         }
-        const unsigned long long act = __ballot(active);
-        if (act == 0ull) break;   // every lane idle (queues are empty): the tile queue is drained
-        c_steps += __popcll(act);
+        if ((run | (unsigned long long)total) == 0ull) break;   // nothing running or queued: the tiles are drained
+        // with the optical-depth-aware step the queued samples are folded before the next step
+        const bool hold = p.tau_step > 0.0 && total > 0;
 
-        // ------------------------------------------------------------ one step of every active ray
-        bool reflected = false;
-        int status = RAY_RUNNING;
-        if (active) {
+        // ------------------------------------------------------------ one step of every running ray
+        bool event = false, reflected = false, want = false;
+        if (__builtin_amdgcn_inverse_ballot_w64(hold ? 0ull : run)) {
             const rk::Spin<double> sp = rk::make_spin(a, M);
             double h = rk::step_size(p.eps, y);
-            if (p.tau_step > 0.0 && rt_rate > 0.0) h = ::fmin(h, p.tau_step / rt_rate);
-            rt_rate = 0.0;
+            if (p.tau_step > 0.0) {
+                double* my_row = row_of(fresh(lane));
+                const double rate = my_row[RATE];
+                if (rate > 0.0) h = ::fmin(h, p.tau_step / rate);
+                my_row[RATE] = 0.0;
+            }
             const double dl = -h;
-            const double th0 = y[2], s0 = sth, c0 = cth;
+            [[maybe_unused]] const double th0 = y[2], s0 = sth, c0 = cth;
             if (INTEG == INTEG_RK2) {
                 rk::rk2_step(sp, y, dl, sth, cth);
             } else if (INTEG == INTEG_VERLET) {
-                if (!have_acc) rk::ks_accel(sp, y, sth, cth, vacc);
+                if (!have_acc) rk::ks_accel<true>(sp, y, sth, cth, vacc);
                 rk::verlet_step(sp, y, vacc, dl, p.integrator == INTEG_VERLET_CORR, sth, cth);
                 have_acc = true;
             } else {
-                rk::rk4_step_angles(sp, y, dl, p.eps <= rk::EPS_CHAINED, &sth, &cth);
+                rk::rk4_step_angles<false>(sp, y, dl, p.eps <= rk::EPS_CHAINED, &sth, &cth);
             }
             ++steps;
-            // a non-finite derivative reaches the wave vector whichever stage it arises in, so the
-            // wave vector alone tells a failed step
-            bool fin = true;
+            // What ends a ray or reflects it at the axis is rare: one test covers it all.  (A
+            // non-finite derivative reaches the wave vector whichever stage it arises in, and the sum
+            // of the four components is finite only if each is.)
+            const bool plain = y[2] >= 0.0 && y[2] <= M_PI && y[1] >= r_stop && y[1] <= r_esc &&
+                               steps < p.max_steps && ::isfinite((y[4] + y[5]) + (y[6] + y[7]));
+            if (!plain) {
+                event = true;
+                bool fin = true;
 #pragma unroll
-            for (int i = 4; i < 8; ++i) fin = fin && ::isfinite(y[i]);
-            if (!fin) {
-                status = RAY_NUMERIC;
-            } else {
-                reflected = rk::reflect_pole(y);
-                if (reflected) have_acc = false;   // the carried derivative belongs to the old chart
-                // sin and cos of the new theta from those of the old one (the step moves theta
-                // little; RK4 has them already); after a reflection from scratch
-                if (reflected)
-                    rt::sincos_small(y[2], &sth, &cth);
-                else if (INTEG != INTEG_RK4)
-                    rk::sincos_shift(th0, s0, c0, y[2], &sth, &cth);
-                if (y[1] < r_stop)
-                    status = RAY_HORIZON;
-                else if (y[1] > r_esc)
-                    status = RAY_ESCAPED;
-                else if (steps >= p.max_steps)
-                    status = RAY_MAXSTEP;
+                for (int i = 4; i < 8; ++i) fin = fin && ::isfinite(y[i]);
+                if (!fin) {
+                    status = RAY_NUMERIC;
+                } else {
+                    reflected = rk::reflect_pole(y);
+                    if (reflected) {
+                        have_acc = false;   // the carried derivative belongs to the old chart
+                        rt::sincos_small(y[2], &sth, &cth);
+                    }
+                    if (y[1] < r_stop)
+                        status = RAY_HORIZON;
+                    else if (y[1] > r_esc)
+                        status = RAY_ESCAPED;
+                    else if (steps >= p.max_steps)
+                        status = RAY_MAXSTEP;
+                }
             }
-            if (status == RAY_RUNNING && pl::in_plasma(p.grids[grid], y[1])) {
-                // queue the sample point
-                const int s = pending * 64 + lane;   // queue layer `pending` of this lane
-                fields[0 * FS + s * SS] = y[0];
-                fields[1 * FS + s * SS] = y[1];
-                fields[2 * FS + s * SS] = y[2];
-                fields[3 * FS + s * SS] = y[3];
-                fields[4 * FS + s * SS] = y[4];
-                fields[5 * FS + s * SS] = y[5];
-                fields[6 * FS + s * SS] = y[7];
-                fields[7 * FS + s * SS] = -dl;
-                fields[8 * FS + s * SS] = sth;
-                fields[9 * FS + s * SS] = cth;
-#pragma unroll
-                for (int k = 0; k < K; ++k)
-                    if (k == pending) qstep[k] = steps;
-                ++pending;
+            // sin and cos of the new theta from those of the old one (the step moves theta little;
+            // RK4 has them already, a reflection forms them from scratch)
+            if (INTEG != INTEG_RK4)
+                if (!reflected && status != RAY_NUMERIC) rk::sincos_shift(th0, s0, c0, y[2], &sth, &cth);
+            if (status == RAY_RUNNING) {
+                // the radial range of the fluid: one for the launch, or the one of the ray's grid
+                double lo = p.r_in, hi = p.r_out;
+                if (!(lo < hi)) {
+                    const DevGrid& gr = p.grids[p.jobs[lane_job[fresh(lane)]].grid];
+                    lo = gr.r_in;
+                    hi = gr.r_out;
+                }
+                want = y[1] >= lo && y[1] <= hi;
+                // the step length waits here for the sample's record (a round may come first)
+                if (want) row_of(fresh(lane))[RATE] = h;
             }
         }
-        c_pole += __popcll(__ballot(reflected));
+        if (!hold) c_steps += __popcll(run);
+        const unsigned long long events = __ballot(event);
+        if (events) {
+            if (reflected) atomicAdd(tally, 1u);
+            const unsigned long long ended = __ballot(status > RAY_RUNNING) & run;
+            run &= ~ended;
+            wait |= ended;
+        }
 
         // ------------------------------------------------------------ evaluate queued samples
-        unsigned total = 0;
+        unsigned long long adds = __ballot(want);
+        const int n_want = __popcll(adds);
+        bool round = total >= 64 || total + n_want > SLOTS || hold;
+        if (!round && total > 0)
+            round = __popcll(wait) >= __popcll(run) ||
+                    (p.tau_cutoff > 0.0 && __ballot(pending() >= CUT_PENDING) != 0ull);
+        if (round) {
+            const TraceParams& p = fresh_params();
+            const int lane = fresh(threadIdx.x & 63);
+            double* my_row = row_of(lane);
+            const int n_eval = total < 64 ? total : 64;
+            const bool has = lane < n_eval;
+            int slot = head + (has ? lane : 0);
+            slot = slot >= SLOTS ? slot - SLOTS : slot;
+            double* rec = ring + slot * REC;
+            // (a lane without a sample reads the oldest one's owner: a lane with a job)
+            const int owner = link_of(ring, slot)[0];
+            double q[N_FIELDS];
 #pragma unroll
-        for (int k = 0; k < K; ++k) total += __popcll(__ballot(pending > k));
-        // a ray that ends with queued samples needs all of them now; a full queue needs one slot;
-        // with the optical-depth-aware step every sample is needed before its ray's next step
-        const bool ending = __ballot(status != RAY_RUNNING && pending > 0) != 0ull || (p.tau_step > 0.0 && total > 0);
-        const bool full = __ballot(pending == K) != 0ull;
-        if (ending || full || total >= 64) {
-            // whole rounds when there are 64 or more (the oldest samples, so a full queue always
-            // gets its first one evaluated), everything when a ray ends or fewer are queued
-            const unsigned n_eval = (ending || total < 64) ? total : (total & ~63u);
-            // select the oldest samples: queue layer k (each lane's k-th sample) before layer k + 1,
-            // within a layer by lane; `take` of this lane's samples are evaluated
-            int take = 0;
-            unsigned listed = 0;
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const unsigned long long b = __ballot(pending > k);
-                const unsigned rank = lane_rank(b);
-                if (pending > k && listed + rank < n_eval) {
-                    slot_map[listed + rank] = k * 64 + lane;
-                    take = k + 1;
-                }
-                const unsigned c = __popcll(b);
-                listed += (c < n_eval - listed) ? c : (n_eval - listed);
+            for (int f = 0; f < N_FIELDS; ++f) q[f] = MLPC && !has ? 1.0 : rec[f];
+            Transfer<TT> tr;
+            MlpSample<TT> ms;
+            int nu_base = 0;
+            bool zamo = false;
+            if (MLPC) {
+                const LaneInfo li = lane_info(p, lane_job[owner]);
+                nu_base = li.nu_base;
+                zamo = ms.setup(p, has, q, li);
+            } else if (has) {
+                const LaneInfo li = lane_info(p, lane_job[owner]);
+                nu_base = li.nu_base;
+                zamo = setup_sample<TT>(p, q, li, tr);
             }
-            wave_lds_sync();
-            if (FUSED) {
-                // phase 1: lane i sets up sample i (fluid, frame, transfer) and leaves the set-up
-                // in the sample's queue slot (K = 1: slot = owner lane, n_eval <= 64)
-                bool zamo = false;
-                if (lane < n_eval) {
-                    const int s = slot_map[lane];
-                    double q[N_FIELDS];
+            c_zamo += __popcll(__ballot(zamo));
+
+            // whether slot s lies among the evaluated samples
+            auto evaluated = [&](int s) {
+                const int d = s - head;
+                return (d < 0 ? d + SLOTS : d) < n_eval;
+            };
+            const bool mine = pending() > 0 && evaluated(first());
+            const unsigned long long rays = __ballot(mine);
+            const int n_rays = __popcll(rays);
+            // Each ray folds its evaluated samples in order, I += exp(-tau) A, tau += dtau: one lane
+            // per ray takes all frequencies of a group, or, when there are lanes for it, one lane per
+            // (ray, frequency).  The cut-off and the optical-depth-aware step look at every frequency
+            // of a sample, so their rays fold in one lane.
+            const bool one_lane = p.tau_cutoff > 0.0 || p.tau_step > 0.0;
+            const bool spread = NNU > 1 && n_rays * G <= 64 && !one_lane;
+            if (spread && mine) ray_tab[lane_rank(rays)] = (unsigned char)lane;
+            int stop = -1;                 // cut-off: slot of the sample that made the ray opaque
+            int nxt = first(), taken = 0;  // after the walk: the ray's oldest sample left and the number folded
+            // The cut-off stops a ray at the first sample behind which every frequency is beyond it.
+            // With several groups that sample (stop_n, counted along the walk) has to be known before
+            // anything is folded.  The group `lead` decides nearly every round by itself: a ray with a
+            // frequency there below the cut-off after all its samples does not stop.  If one is left
+            // in question the other groups are evaluated too, and then all of them again to be folded.
+            const bool groups = NNU > FREQ_GROUP && p.tau_cutoff > 0.0 && p.n_nu > G;
+            bool probe = groups, question = mine;
+            int stop_n = 0;
+            for (int k = 0, f0 = groups && p.tau_step == 0.0 ? lead : 0; k < p.n_nu;) {
+                const int cnt = p.n_nu - f0;
+                double A[G], dt[G];
 #pragma unroll
-                    for (int f = 0; f < N_FIELDS; ++f) q[f] = fields[f * FS + s * SS];
-                    Transfer<TT> tr;
-                    zamo = setup_sample<TT>(p, q, lane_info(p, lane_job[s]), tr);
-                    store_setup<TT, FS, SS>(fields, s, tr);
+                for (int g = 0; g < G; ++g) {
+                    A[g] = 0.0;
+                    dt[g] = 0.0;
                 }
-                c_zamo += __popcll(__ballot(zamo));
-                wave_lds_sync();
-                // phase 2: `per` consecutive lanes share a sample, lane c of them taking its
-                // frequencies [c n, (c + 1) n), n = ceil(n_nu / per): contribution, then the fold
-                // I += exp(-tau) A, tau += dtau into the owner's row
-                const unsigned per = n_eval >= 64 ? 1u : (64u / n_eval < (unsigned)NNU ? 64u / n_eval : (unsigned)NNU);
-                const unsigned mul = (65535u + per) / per;   // x / per = (x mul) >> 16 for x < 1024
-                const unsigned is = ((unsigned)lane * mul) >> 16;
-                const unsigned chunk = (unsigned)lane - is * per;
-                double tmin = 1e300, dtmax = 0.0;
-                if (is < n_eval) {
-                    const int s = slot_map[is];
-                    const LaneInfo li = lane_info(p, lane_job[s]);
-                    const int c = (int)(((unsigned)(li.n_nu + per - 1) * mul) >> 16);
-                    const int f0 = (int)chunk * c;
-                    const int f1 = (f0 + c < li.n_nu) ? f0 + c : li.n_nu;
-                    Transfer<TT> tr;
-                    load_setup<TT, FS, SS>(fields, s, tr);
-                    double* Ir = res + s * RS;
-                    double* Tr = Ir + NNU;
-                    constexpr int G = NNU < FREQ_GROUP ? NNU : FREQ_GROUP;
-                    int f = f0;
-                    for (; f + G <= f1; f += G) {
-                        double nu[G], A[G], dt[G], t0[G];
-                        TT att[G];   // formed before the contributions, so that the chains overlap
+                if (MLPC) {
+                    if (NNU == 1) {
+                        ms.contribution(p, lds_net, p.nu[nu_base], A[0], dt[0], c_fallback, c_dropped);
+                    } else {
+#pragma unroll 1
+                        for (int g = 0; g < G && g < cnt; ++g) {
+                            double Ag, dg;
+                            ms.contribution(p, lds_net, p.nu[nu_base + f0 + g], Ag, dg, c_fallback, c_dropped);
 #pragma unroll
-                        for (int g = 0; g < G; ++g) {
-                            nu[g] = p.nu[li.nu_base + f + g];
-                            A[g] = 0.0;
-                            dt[g] = 0.0;
-                            t0[g] = Tr[f + g];
-                            att[g] = attenuation<TT>(t0[g]);
-                        }
-                        tr.template contributions<G>(p, nu, G, A, dt);
-#pragma unroll
-                        for (int g = 0; g < G; ++g) {
-                            Ir[f + g] = Ir[f + g] + (double)att[g] * A[g];
-                            const double t1 = t0[g] + dt[g];
-                            Tr[f + g] = t1;
-                            tmin = ::fmin(tmin, t1);
-                            dtmax = ::fmax(dtmax, dt[g]);
-                        }
-                    }
-                    for (; f < f1; ++f) {   // the rest one at a time, in the branch-free form
-                        double A = 0.0, dt = 0.0;
-                        const double nu1 = p.nu[li.nu_base + f];
-                        tr.template contributions<1, false>(p, &nu1, 1, &A, &dt);
-                        const double t0 = Tr[f];
-                        Ir[f] = Ir[f] + (double)attenuation<TT>(t0) * A;
-                        const double t1 = t0 + dt;
-                        Tr[f] = t1;
-                        tmin = ::fmin(tmin, t1);
-                        dtmax = ::fmax(dtmax, dt);
-                    }
-                }
-                // the sample's smallest optical depth and largest step depth over its frequencies:
-                // reduced over its `per` lanes onto the first, which leaves them in the slot's
-                // queue fields 8 and 9 (the set-up is no longer read)
-                for (unsigned off = 1; off < per; off <<= 1) {
-                    const double tm = __shfl_down(tmin, off, 64), dm = __shfl_down(dtmax, off, 64);
-                    if (chunk + off < per) {
-                        tmin = ::fmin(tmin, tm);
-                        dtmax = ::fmax(dtmax, dm);
-                    }
-                }
-                if (is < n_eval && chunk == 0) {
-                    const int s = slot_map[is];
-                    fields[8 * FS + s * SS] = tmin;
-                    fields[9 * FS + s * SS] = dtmax;
-                }
-            } else if (!MLPC && NNU > 1 && n_eval < 64) {
-                // fewer samples than lanes: the (sample, frequency) pairs are spread over the
-                // wave.  Lane i sets up sample i (fluid, frame, transfer) and leaves the set-up
-                // in the sample's queue slot; then `per` lanes share each sample, lane c of them
-                // taking its frequencies [c n, (c + 1) n), n = ceil(n_nu / per).
-                bool zamo = false;
-                if (lane < n_eval) {
-                    const int s = slot_map[lane];
-                    double q[N_FIELDS];
-#pragma unroll
-                    for (int f = 0; f < N_FIELDS; ++f) q[f] = fields[f * FS + s * SS];
-                    Transfer<TT> tr;
-                    zamo = setup_sample<TT>(p, q, lane_info(p, lane_job[s & 63]), tr);
-                    store_setup<TT, FS, SS>(fields, s, tr);
-                }
-                c_zamo += __popcll(__ballot(zamo));
-                wave_lds_sync();
-                const unsigned per = (64u / n_eval < (unsigned)NNU) ? 64u / n_eval : (unsigned)NNU;
-                const unsigned mul = (65535u + per) / per;   // x / per = (x mul) >> 16 for x < 1024
-                const unsigned is = ((unsigned)lane * mul) >> 16;
-                if (is < n_eval) {
-                    const int s = slot_map[is];
-                    const LaneInfo li = lane_info(p, lane_job[s & 63]);
-                    const int c = (int)(((unsigned)(li.n_nu + per - 1) * mul) >> 16);
-                    const int f0 = (int)((unsigned)lane - is * per) * c;
-                    const int f1 = (f0 + c < li.n_nu) ? f0 + c : li.n_nu;
-                    Transfer<TT> tr;
-                    load_setup<TT, FS, SS>(fields, s, tr);
-                    constexpr int G = NNU < FREQ_GROUP ? NNU : FREQ_GROUP;
-                    for (int f = f0; f < f1; f += G) {
-                        const int cnt = f1 - f;
-                        double nu[G], A[G], dt[G];
-#pragma unroll
-                        for (int g = 0; g < G; ++g) {
-                            nu[g] = g < cnt ? p.nu[li.nu_base + f + g] : 1.0;
-                            A[g] = 0.0;
-                            dt[g] = 0.0;
-                        }
-                        tr.template contributions<G>(p, nu, cnt, A, dt);
-#pragma unroll
-                        for (int g = 0; g < G; ++g) {
-                            if (g < cnt) {
-                                res[s * RS + f + g] = A[g];
-                                res[s * RS + NNU + f + g] = dt[g];
+                            for (int k = 0; k < G; ++k) {
+                                A[k] = k == g ? Ag : A[k];
+                                dt[k] = k == g ? dg : dt[k];
                             }
                         }
                     }
+                } else if (has) {
+                    if (NNU == 1) {
+                        tr.contribution(p, p.nu[nu_base], A[0], dt[0]);
+                    } else {
+                        double nu[G];
+#pragma unroll
+                        for (int g = 0; g < G; ++g) nu[g] = g < cnt ? p.nu[nu_base + f0 + g] : 1.0;
+                        tr.template contributions<G>(p, nu, cnt, A, dt);
+                    }
                 }
-            } else
-            for (unsigned r0 = 0; r0 < n_eval; r0 += 64) {
-                const unsigned i = r0 + lane;
-                if (MLPC) {
-                    // every lane takes part in the network evaluations of the round
-                    const bool has = i < n_eval;
-                    const int s = has ? slot_map[i] : 0;
-                    double q[N_FIELDS];
+                if (has) {
 #pragma unroll
-                    for (int f = 0; f < N_FIELDS; ++f) q[f] = has ? fields[f * FS + s * SS] : 1.0;
-                    double A[NNU], dt[NNU];
-                    eval_round_mlp<NNU, TT>(p, lds_net, has, q, lane_info(p, lane_job[s & 63]), A, dt, c_zamo,
-                                            c_fallback, c_dropped);
-                    if (has) {
+                    for (int g = 0; g < G; ++g) {
+                        rec[g] = A[g];
+                        rec[G + g] = dt[g];
+                    }
+                }
+                wave_lds_sync();
+                if (NNU > FREQ_GROUP && probe) {
+                    double t0[G];
 #pragma unroll
-                        for (int f = 0; f < NNU; ++f) {
-                            res[s * RS + f] = A[f];
-                            res[s * RS + NNU + f] = dt[f];
+                    for (int g = 0; g < G; ++g) t0[g] = question && g < cnt ? my_row[f0 + COLS + g] : 0.0;
+                    int s = first(), n = 0;
+                    bool more = question, opaque = false;
+                    while (__ballot(more)) {
+                        if (more) {
+                            const double* r = ring + s * REC;
+                            double t1 = 1e300;
+#pragma unroll
+                            for (int g = 0; g < G; ++g) {
+                                t0[g] = t0[g] + r[G + g];
+                                t1 = g < cnt ? ::fmin(t1, t0[g]) : t1;
+                            }
+                            ++n;
+                            opaque = t1 >= p.tau_cutoff;
+                            s = link_of(ring, s)[1];
+                            more = !opaque && pending() > n && evaluated(s);
+                        }
+                    }
+                    question = question && opaque;
+                    if (question) stop_n = n > stop_n ? n : stop_n;
+                    wave_lds_sync();
+                    const bool none = __ballot(question) == 0ull;
+                    if (none && k == 0) {
+                        probe = false;   // this evaluation is folded at once
+                    } else {
+                        if (none) lead = f0;
+                        probe = !none && k + G < p.n_nu;
+                        k = probe ? k + G : 0;
+                        f0 = probe ? (f0 + G < p.n_nu ? f0 + G : 0) : p.tau_step > 0.0 ? 0 : lead;
+                        continue;
+                    }
+                }
+                if (spread) {
+                    const int j = lane / G, g = lane % G;
+                    const bool on = j < n_rays && g < cnt;
+                    const int o = on ? ray_tab[j] : 0;
+                    const unsigned oq = __shfl(queued, o, 64);
+                    int s = (int)(oq & 255u), left = (int)(oq >> 16);
+                    double* row = rows + o * ROW + f0 + g;
+                    double It = 0.0, t0 = 0.0;
+                    if (on) {
+                        It = row[0];
+                        t0 = row[COLS];
+                    }
+                    bool more = on;
+                    while (__ballot(more)) {
+                        if (more) {
+                            const double* r = ring + s * REC;
+                            It = __builtin_fma((double)attenuation<TT>(t0), r[g], It);
+                            t0 = t0 + r[G + g];
+                            s = link_of(ring, s)[1];
+                            more = --left > 0 && evaluated(s);
+                        }
+                    }
+                    if (on) {
+                        row[0] = It;
+                        row[COLS] = t0;
+                        if (f0 == 0 && g == 0) {
+                            ray_next[o] = (unsigned char)s;
+                            ray_left[o] = (unsigned char)left;
                         }
                     }
                 } else {
-                    bool zamo = false;
-                    if (i < n_eval) {
-                        const int s = slot_map[i];
-                        double q[N_FIELDS];
+                    double* row = my_row + f0;
+                    double It[G], t0[G];
 #pragma unroll
-                        for (int f = 0; f < N_FIELDS; ++f) q[f] = fields[f * FS + s * SS];
-                        double A[NNU], dt[NNU];
-                        zamo = eval_sample<NNU, TT>(p, q, lane_info(p, lane_job[s & 63]), A, dt);
+                    for (int g = 0; g < G; ++g) {
+                        It[g] = mine && g < cnt ? row[g] : 0.0;
+                        t0[g] = mine && g < cnt ? row[COLS + g] : 0.0;
+                    }
+                    nxt = first();
+                    taken = 0;
+                    bool more = mine;
+                    while (__ballot(more)) {
+                        if (one_lane && f0 == 0) c_samples += __popcll(__ballot(more));
+                        if (more) {
+                            const int s = nxt;
+                            const double* r = ring + s * REC;
+                            nxt = link_of(ring, s)[1];
+                            double t1 = 1e300;
 #pragma unroll
-                        for (int f = 0; f < NNU; ++f) {
-                            res[s * RS + f] = A[f];
-                            res[s * RS + NNU + f] = dt[f];
+                            for (int g = 0; g < G; ++g) {
+                                It[g] = __builtin_fma((double)attenuation<TT>(t0[g]), r[g], It[g]);
+                                t0[g] = t0[g] + r[G + g];
+                                t1 = g < cnt ? ::fmin(t1, t0[g]) : t1;
+                            }
+                            ++taken;
+                            more = pending() > taken && evaluated(nxt);
+                            // cut-off: with one group, every frequency of the sample is known here
+                            if (groups ? question && taken == stop_n : p.tau_cutoff > 0.0 && t1 >= p.tau_cutoff) {
+                                stop = s;
+                                more = false;
+                            }
                         }
                     }
-                    c_zamo += __popcll(__ballot(zamo));
+                    if (p.tau_step > 0.0 && mine) {   // one sample per ray and round
+                        double d1 = f0 == 0 ? 0.0 : my_row[RATE];
+#pragma unroll
+                        for (int g = 0; g < G; ++g) d1 = ::fmax(d1, ring[first() * REC + G + g]);
+                        my_row[RATE] = f0 + G < p.n_nu ? d1 : d1 / ring[first() * REC + F_DL];
+                    }
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        if (mine && g < cnt) {
+                            row[g] = It[g];
+                            row[COLS + g] = t0[g];
+                        }
+                    }
                 }
+                wave_lds_sync();
+                k += G;
+                f0 = f0 + G < p.n_nu ? f0 + G : 0;
             }
-            c_samples += n_eval;
-            wave_lds_sync();
-            // each owner folds its evaluated samples in order: I += exp(-tau) A, tau += dtau; with
-            // the optical-depth cut-off the ray ends after the first sample that makes it opaque
-            // at every frequency, and its later queued samples are dropped
-            bool cut = false;
-            if (FUSED && take > 0) {
-                const int s = lane;   // K = 1
-                if (p.tau_step > 0.0) rt_rate = fields[9 * FS + s * SS] / fields[7 * FS + s * SS];
-                if (p.tau_cutoff > 0.0 && fields[8 * FS + s * SS] >= p.tau_cutoff) {
-                    cut = true;
+            // each ray leaves the folded samples behind; one found opaque stops at that sample
+            if (!one_lane) c_samples += n_eval;
+            if (mine) {
+                const int left = spread ? ray_left[lane] : pending() - taken;
+                queued = (queued & 0xff00u) | ((unsigned)left << 16) | (unsigned)(spread ? ray_next[lane] : nxt);
+                if (stop >= 0) {
+                    const int at = *reinterpret_cast<const int*>(link_of(ring, stop) + REC_STEP - REC_LINK);
+                    atomicAdd(p.stats + ST_STEPS, (unsigned long long)(at - steps));   // steps beyond the stop
                     status = RAY_OPAQUE;
-                    steps = qstep[0];
+                    steps = at;
+                    queued = 0;
                 }
             }
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                if (!FUSED && k < take && !cut) {
-                    const int s = k * 64 + lane;
-                    double tmin = 1e300, dtmax = 0.0;
-#pragma unroll
-                    for (int f = 0; f < NNU; ++f) {
-                        if (f < n_nu) {
-                            I[f] = I[f] + (double)attenuation<TT>(tau[f]) * res[s * RS + f];
-                            tau[f] = tau[f] + res[s * RS + NNU + f];
-                            tmin = ::fmin(tmin, tau[f]);
-                            dtmax = ::fmax(dtmax, res[s * RS + NNU + f]);
-                        }
-                    }
-                    // d tau / d|lambda| of this sample (the last one folded sets the next step)
-                    if (p.tau_step > 0.0) rt_rate = dtmax / fields[7 * FS + s * SS];
-                    if (p.tau_cutoff > 0.0 && tmin >= p.tau_cutoff) {
-                        cut = true;
-                        status = RAY_OPAQUE;
-                        steps = qstep[k];
-                    }
-                }
+            if (p.tau_cutoff > 0.0) {
+                const unsigned long long ended = __ballot(status > RAY_RUNNING) & run;
+                run &= ~ended;
+                wait |= ended;
+                adds &= run;   // a ray found opaque at an earlier sample queues no more
             }
-            // move the samples left queued to the front of this lane's queue
-            const int left = cut ? 0 : pending - take;
-            if (K > 1 && take > 0) {
-#pragma unroll
-                for (int j = 0; j + 1 < K; ++j) {
-                    if (j < left) {
-#pragma unroll
-                        for (int f = 0; f < N_FIELDS; ++f)
-                            fields[f * FS + (j * 64 + lane) * SS] = fields[f * FS + ((j + take) * 64 + lane) * SS];
-                    }
-                }
-#pragma unroll
-                for (int j = 0; j + 1 < K; ++j) {
-                    int v = qstep[j];
-#pragma unroll
-                    for (int m = 1; m < K; ++m)
-                        if (m == take && j + m < K) v = qstep[j + m];
-                    qstep[j] = v;
-                }
-            }
-            pending = left;
+            head += n_eval;
+            head = head >= SLOTS ? head - SLOTS : head;
+            total -= n_eval;
             wave_lds_sync();
         }
 
-        // ------------------------------------------------------------ finished rays
-        if (status != RAY_RUNNING) {
-            const DevJob& J = p.jobs[job];
-            const long long npix = (long long)J.nx * J.ny;
-            double* o = p.out + J.out_base + pix;
-#pragma unroll
-            for (int f = 0; f < NNU; ++f)
-                if (f < n_nu) o[f * npix] = (status == RAY_NUMERIC) ? 0.0 : (FUSED ? res[lane * RS + f] : I[f]);
-            if (p.ray_status) p.ray_status[J.pix_base + pix] = status;
-            if (p.ray_steps) p.ray_steps[J.pix_base + pix] = steps;
-            active = false;
+        // ------------------------------------------------------------ queue this step's samples
+        if (__builtin_amdgcn_inverse_ballot_w64(adds)) {
+            const int lane = fresh(threadIdx.x & 63);
+            int s = head + total + (int)lane_rank(adds);
+            s = s >= SLOTS ? s - SLOTS : s;
+            double* rec = ring + s * REC;
+            rec[0] = y[0];
+            rec[1] = y[1];
+            rec[2] = y[2];
+            rec[3] = y[3];
+            rec[4] = y[4];
+            rec[5] = y[5];
+            rec[6] = y[7];
+            rec[7] = sth;
+            rec[8] = cth;
+            rec[F_DL] = row_of(lane)[RATE];
+            unsigned char* l = link_of(ring, s);
+            *reinterpret_cast<int*>(l) = lane;
+            *reinterpret_cast<int*>(l + REC_STEP - REC_LINK) = steps;
+            if (pending() > 0)
+                link_of(ring, (int)((queued >> 8) & 255u))[1] = (unsigned char)s;
+            else
+                queued = (unsigned)s;
+            queued = ((queued + 0x10000u) & ~0xff00u) | ((unsigned)s << 8);
         }
-        const unsigned long long done = __ballot(status != RAY_RUNNING);
-        if (done) {
-            c_rays += __popcll(done);
-            c_hor += __popcll(__ballot(status == RAY_HORIZON));
-            c_esc += __popcll(__ballot(status == RAY_ESCAPED));
-            c_max += __popcll(__ballot(status == RAY_MAXSTEP));
-            c_num += __popcll(__ballot(status == RAY_NUMERIC));
-            c_opq += __popcll(__ballot(status == RAY_OPAQUE));
+        total += __popcll(adds);
+        wave_lds_sync();
+
+        // ------------------------------------------------------------ finished rays
+        if (wait != 0ull && (events != 0ull || round)) {
+            const bool finished = status > RAY_RUNNING && pending() == 0;
+            const unsigned long long done = __ballot(finished);
+            const TraceParams& p = fresh_params();
+            if (finished) {
+                const int lane = fresh(threadIdx.x & 63);
+                const double* my_row = row_of(lane);
+                const DevJob& J = p.jobs[lane_job[lane]];
+                const int pix = lane_pix[lane];
+                const long long npix = (long long)J.nx * J.ny;
+                double* o = p.out + J.out_base + pix;
+                for (int f = 0; f < p.n_nu; ++f) o[f * npix] = (status == RAY_NUMERIC) ? 0.0 : my_row[f];
+                if (p.ray_status) p.ray_status[J.pix_base + pix] = status;
+                if (p.ray_steps) p.ray_steps[J.pix_base + pix] = steps;
+                atomicAdd(tally + status, 1u);
+                status = RAY_IDLE;
+            }
+            wait &= ~done;
+            idle_changed = done != 0ull;
         }
     }
 
     // ------------------------------------------------------------ statistics, one atomic per counter per wave
+    wave_lds_sync();
     if (lane == 0) {
-        const unsigned long long st[ST_COUNT] = {c_rays, c_steps, c_samples, c_hor, c_esc, c_max, c_pole, c_num,
-                                                 c_fallback, c_zamo, c_opq, c_dropped};
+        const TraceParams& p = fresh_params();
+        unsigned long long rays = 0;
+#pragma unroll
+        for (int i = RAY_HORIZON; i <= RAY_OPAQUE; ++i) rays += tally[i];
+        const unsigned long long st[ST_COUNT] = {rays, c_steps, c_samples, tally[RAY_HORIZON], tally[RAY_ESCAPED],
+                                                 tally[RAY_MAXSTEP], tally[0], tally[RAY_NUMERIC], c_fallback, c_zamo,
+                                                 tally[RAY_OPAQUE], c_dropped};
 #pragma unroll
         for (int i = 0; i < ST_COUNT; ++i)
             if (st[i]) atomicAdd(p.stats + i, st[i]);
@@ -1049,9 +1048,9 @@ __global__ void flux_final_kernel(const DevJob* jobs, const double* part, const 
     flux[jf] = s * pix_sr[job] * 1e23;
 }
 
-__global__ void reset_kernel(unsigned int* tile_counter, unsigned long long* stats)
+__global__ void reset_kernel(unsigned long long* ray_counter, unsigned long long first, unsigned long long* stats)
 {
-    if (threadIdx.x == 0) *tile_counter = 0u;
+    if (threadIdx.x == 0) *ray_counter = first;
     if (threadIdx.x < ST_COUNT) stats[threadIdx.x] = 0ull;
 }
 
@@ -1091,16 +1090,15 @@ const void* symbol_tt(int max_nu, int wpe, bool mlpc, int integ)
 {
     if (max_nu <= 1) return symbol_of<1, TT>(wpe, mlpc, integ);
     if (max_nu <= 4) return symbol_of<4, TT>(wpe, mlpc, integ);
-    if (max_nu <= 8) return symbol_of<8, TT>(wpe, mlpc, integ);
-    if (max_nu <= 16) return symbol_of<16, TT>(wpe, mlpc, integ);
     return symbol_of<32, TT>(wpe, mlpc, integ);
 }
 
 }  // namespace
 
-hipError_t launch_reset(unsigned int* tile_counter, unsigned long long* stats, hipStream_t st)
+hipError_t launch_reset(unsigned long long* ray_counter, unsigned long long first, unsigned long long* stats,
+                        hipStream_t st)
 {
-    hipLaunchKernelGGL(reset_kernel, dim3(1), dim3(64), 0, st, tile_counter, stats);
+    hipLaunchKernelGGL(reset_kernel, dim3(1), dim3(64), 0, st, ray_counter, first, stats);
     return hipGetLastError();
 }
 
@@ -1109,7 +1107,7 @@ hipError_t launch_trace(const TraceParams& p, int max_nu, bool fp32, int wpe, in
     const void* fn = trace_kernel_symbol(max_nu, fp32, wpe, p.closure >= CL_MLP, p.integrator);
     void* args[] = {const_cast<TraceParams*>(&p)};
     return hipLaunchKernel(fn, dim3(blocks), dim3(threads), args,
-                           trace_kernel_lds(max_nu, fp32, wpe, threads, p.closure >= CL_MLP, p.integrator,
+                           trace_kernel_lds(p.n_nu, wpe, threads, p.closure >= CL_MLP, p.integrator,
                                             p.rays_per_wave),
                            st);
 }
@@ -1131,35 +1129,38 @@ hipError_t launch_flux(const DevJob* jobs, int n_jobs, const double* out, const 
 
 // Visit the queue type of the instantiation that trace_kernel_symbol picks for the same arguments.
 template <class F>
-auto with_queue(int max_nu, bool fp32, int wpe, bool mlpc, int integ, F f)
+auto with_queue(int n_nu, int wpe, bool mlpc, int integ, F f)
 {
     const int w = kernel_wpe(wpe, mlpc, integ);
-    auto per_w = [&](auto tt, auto m, auto w) {
-        using TT = decltype(tt);
+    auto per_w = [&](auto m, auto w) {
         constexpr bool M = decltype(m)::value;
         constexpr int W = decltype(w)::value;
-        if (max_nu <= 1) return f(Queue<1, TT, M, W>{});
-        if (max_nu <= 4) return f(Queue<4, TT, M, W>{});
-        if (max_nu <= 8) return f(Queue<8, TT, M, W>{});
-        if (max_nu <= 16) return f(Queue<16, TT, M, W>{});
-        return f(Queue<32, TT, M, W>{});
+        if (n_nu <= 1) return f(Queue<1, M, W>{});
+        if (n_nu <= 4) return f(Queue<4, M, W>{});
+        return f(Queue<32, M, W>{});
     };
-    auto per_q = [&](auto tt, auto m) {
-        return w == 3 ? per_w(tt, m, std::integral_constant<int, 3>{}) : per_w(tt, m, std::integral_constant<int, 2>{});
+    auto per = [&](auto m) {
+        return w == 3 ? per_w(m, std::integral_constant<int, 3>{})
+             : w == 2 ? per_w(m, std::integral_constant<int, 2>{}) : per_w(m, std::integral_constant<int, 1>{});
     };
-    auto per = [&](auto tt) { return mlpc ? per_q(tt, std::true_type{}) : per_q(tt, std::false_type{}); };
-    return fp32 ? per(0.0f) : per(0.0);
+    return mlpc ? per(std::true_type{}) : per(std::false_type{});
 }
 
-bool trace_kernel_one_slot(int max_nu, bool fp32, int wpe, bool mlpc, int integ)
+bool trace_plan_takes_rays(int max_nu, int wpe, bool mlpc, int integ)
 {
-    return !mlpc && max_nu > 1 && with_queue(max_nu, fp32, wpe, mlpc, integ, [](auto q) { return decltype(q)::K == 1; });
+    return !mlpc && (max_nu > 4 || (max_nu > 1 && kernel_wpe(wpe, mlpc, integ) == 3));
 }
 
-size_t trace_kernel_lds(int max_nu, bool fp32, int wpe, int threads, bool mlpc, int integ, int rays)
+int trace_kernel_slots(int n_nu, int wpe, bool mlpc, int integ, int rays)
 {
-    const size_t per_wave =
-        with_queue(max_nu, fp32, wpe, mlpc, integ, [&](auto q) { return decltype(q)::per_wave(rays); });
+    return with_queue(n_nu, wpe, mlpc, integ, [&](auto q) { return decltype(q)::slots(rays, n_nu); });
+}
+
+size_t trace_kernel_lds(int n_nu, int wpe, int threads, bool mlpc, int integ, int rays)
+{
+    const size_t per_wave = with_queue(n_nu, wpe, mlpc, integ, [&](auto q) {
+        return decltype(q)::per_wave(rays, decltype(q)::slots(rays, n_nu), n_nu);
+    });
     return (size_t)(threads / 64) * per_wave + (mlpc ? (size_t)mlp::LDS_NET_BYTES : 0);
 }
 
