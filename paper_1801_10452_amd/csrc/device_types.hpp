@@ -95,4 +95,5 @@ struct DiskParams {
     int* status;                  // [ny][nx] or null
     int* steps;                   // [ny][nx] or null
     unsigned long long* stats;    // [0] ray-steps, [1] rays on the disk
+    unsigned long long* counter;  // next tile to hand out
 };

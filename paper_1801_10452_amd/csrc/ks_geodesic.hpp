@@ -520,7 +520,7 @@ __host__ __device__ inline bool rk4_try_chained(const Spin<double>& sp, double* 
 
 // One RK4 step and the sine and cosine of theta with it (those of y[2] on entry and on return):
 // SHORT the chained form, else rk4_step's own operations; `block`: eps is small enough for either.
-template <bool SHORT>
+template <bool SHORT = true>
 __host__ __device__ inline void rk4_step_angles(const Spin<double>& sp, double* y, double dl, bool block,
                                                 double* sin_th, double* cos_th)
 {

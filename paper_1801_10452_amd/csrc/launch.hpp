@@ -34,9 +34,12 @@ bool trace_plan_takes_rays(int max_nu, int wpe, bool mlpc, int integ);
 int kernel_wpe(int wpe, bool mlpc, int integ);
 
 // ---- thin disk (disk.hip)
+constexpr int DISK_THREADS = 64;
 hipError_t launch_disk(const DiskParams& p, int blocks, hipStream_t st);
+// part: disk_profile_chunks(n, n_bins) * n_bins doubles
+int disk_profile_chunks(long long n, int n_bins);
 hipError_t launch_disk_profile(const double* intensity, const double* redshift, long long n, int n_bins, double g_lo,
-                               double g_hi, double dA, double* profile, hipStream_t st);
+                               double g_hi, double dA, double* part, double* profile, hipStream_t st);
 
 // ---- learned closure (mlp.hip)
 namespace mlp {
