@@ -70,6 +70,9 @@ struct LaunchPlan {
     int resident = 1;   // work-groups that a compute unit's registers and wave slots hold at once
 };
 
+// Scratch that outlives a call: 64 MB (a larger one is freed when the call returns).
+constexpr size_t SCRATCH_KEPT = size_t(1) << 24;
+
 // Learned closure: FP32 parameters with Adam moments, padded BF16 copies, training samples.
 struct MlpState {
     bool ready = false;
@@ -78,12 +81,14 @@ struct MlpState {
     DevBuf<unsigned short> W, Wlo, WT;
     DevBuf<float> partial, loss;
     DevBuf<float> Xtr, Ttr, Xva, Tva, RAWva;
+    DevBuf<float> scratch;   // of the calls on host arrays, up to SCRATCH_KEPT floats
     long long n_train = 0, n_val = 0;
     unsigned long long train_seed = 0, val_seed = 0;
     void release()
     {
         P.release(); m.release(); v.release(); W.release(); Wlo.release(); WT.release();
         partial.release(); loss.release(); Xtr.release(); Ttr.release(); Xva.release(); Tva.release(); RAWva.release();
+        scratch.release();
     }
 };
 

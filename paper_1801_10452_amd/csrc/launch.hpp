@@ -56,6 +56,9 @@ hipError_t mlp_launch_train(const mlp::Net& net, const float* X, const float* T,
 hipError_t mlp_launch_reduce(const float* partial, int n_waves, int mode, float* P, float* m, float* v, float lr,
                              float b1, float b2, float eps, float wd, float bc1, float bc2, float* grad_out,
                              unsigned short* W, unsigned short* Wlo, unsigned short* WT, hipStream_t st);
+// network inputs from raw ones [n][3], and (ln j_hat, ln alpha_hat) from the network's outputs, in place
+hipError_t mlp_launch_net_inputs(const float* raw, long long n, float* X, hipStream_t st);
+hipError_t mlp_launch_net_outputs(const float* raw, long long n, float* Y, hipStream_t st);
 hipError_t mlp_launch_forward(const mlp::Net& net, bool split, const float* X, long long n, float* Y, hipStream_t st);
 hipError_t mlp_launch_forward_f32(const float* P, const float* X, long long n, float* Y, hipStream_t st);
 hipError_t mlp_launch_backward_f32(const float* P, const float* X, const float* DY, long long n, float* G,

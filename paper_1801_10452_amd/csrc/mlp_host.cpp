@@ -101,6 +101,34 @@ raptor_status ensure_samples(raptor_ctx* ctx, DevBuf<float>& X, DevBuf<float>& T
     return RAPTOR_OK;
 }
 
+// Device arrays of one call on host arrays: the context's scratch, or, beyond what it keeps, memory
+// freed with the object (four allocations and frees a call took up to 0.1 ms).  Every call waits for
+// its work before it returns.
+struct Scratch {
+    DevBuf<float> own;
+    float* base = nullptr;
+    size_t at[5] = {0, 0, 0, 0, 0};
+    hipError_t error;
+    Scratch(raptor_ctx* ctx, std::initializer_list<size_t> sizes)
+    {
+        int k = 0;
+        for (size_t n : sizes) {
+            at[k + 1] = at[k] + (n + 63) / 64 * 64;
+            ++k;
+        }
+        DevBuf<float>& b = at[k] <= SCRATCH_KEPT ? ctx->mlp.scratch : own;
+        error = b.reserve(at[k]);
+        base = b.p;
+    }
+    float* operator[](int k) const { return base + at[k]; }
+};
+
+hipError_t launch_net(raptor_ctx* ctx, int form, const float* X, long long n, float* Y)
+{
+    if (form == RAPTOR_MLP_F32) return mlp_launch_forward_f32(ctx->mlp.P.p, X, n, Y, ctx->stream);
+    return mlp_launch_forward(net_of(ctx->mlp), form == RAPTOR_MLP_SPLIT, X, n, Y, ctx->stream);
+}
+
 bool form_ok(int f) { return f == RAPTOR_MLP_SPLIT || f == RAPTOR_MLP_BF16 || f == RAPTOR_MLP_F32; }
 
 }  // namespace
@@ -323,19 +351,13 @@ raptor_status raptor_mlp_forward(raptor_ctx* ctx, int32_t form, const float* x, 
     raptor_status s = need_ready(ctx);
     if (s != RAPTOR_OK) return s;
     RAPTOR_CK(hipSetDevice(ctx->device), "selecting the device");
-    DevBuf<float> X, Y;
-    RAPTOR_CK(X.reserve((size_t)3 * n), "allocating inputs");
-    RAPTOR_CK(Y.reserve((size_t)2 * n), "allocating outputs");
-    RAPTOR_CK(hipMemcpyAsync(X.p, x, (size_t)12 * n, hipMemcpyHostToDevice, ctx->stream), "uploading inputs");
-    if (form == RAPTOR_MLP_F32)
-        RAPTOR_CK(mlp_launch_forward_f32(ctx->mlp.P.p, X.p, n, Y.p, ctx->stream), "launching the forward pass");
-    else
-        RAPTOR_CK(mlp_launch_forward(net_of(ctx->mlp), form == RAPTOR_MLP_SPLIT, X.p, n, Y.p, ctx->stream),
-                  "launching the forward pass");
-    RAPTOR_CK(hipMemcpyAsync(y, Y.p, (size_t)8 * n, hipMemcpyDeviceToHost, ctx->stream), "reading outputs");
+    Scratch b(ctx, {(size_t)3 * n, (size_t)2 * n});
+    RAPTOR_CK(b.error, "allocating inputs and outputs");
+    float *X = b[0], *Y = b[1];
+    RAPTOR_CK(hipMemcpyAsync(X, x, (size_t)12 * n, hipMemcpyHostToDevice, ctx->stream), "uploading inputs");
+    RAPTOR_CK(launch_net(ctx, form, X, n, Y), "launching the forward pass");
+    RAPTOR_CK(hipMemcpyAsync(y, Y, (size_t)8 * n, hipMemcpyDeviceToHost, ctx->stream), "reading outputs");
     RAPTOR_CK(hipStreamSynchronize(ctx->stream), "running the forward pass");
-    X.release();
-    Y.release();
     return RAPTOR_OK;
 }
 
@@ -350,32 +372,24 @@ raptor_status raptor_mlp_backward(raptor_ctx* ctx, int32_t form, const float* x,
     if (s != RAPTOR_OK) return s;
     RAPTOR_CK(hipSetDevice(ctx->device), "selecting the device");
     MlpState& S = ctx->mlp;
-    DevBuf<float> X, D, G;
-    RAPTOR_CK(X.reserve((size_t)3 * n), "allocating inputs");
-    RAPTOR_CK(D.reserve((size_t)2 * n), "allocating inputs");
-    RAPTOR_CK(G.reserve(NP), "allocating gradients");
-    RAPTOR_CK(hipMemcpyAsync(X.p, x, (size_t)12 * n, hipMemcpyHostToDevice, ctx->stream), "uploading inputs");
-    RAPTOR_CK(hipMemcpyAsync(D.p, dy, (size_t)8 * n, hipMemcpyHostToDevice, ctx->stream), "uploading inputs");
+    const int waves = form == RAPTOR_MLP_F32 ? 0 : (int)((n + 63) / 64);
+    Scratch b(ctx, {(size_t)3 * n, (size_t)2 * n, (size_t)NP, (size_t)waves * NP});
+    RAPTOR_CK(b.error, "allocating inputs and gradients");
+    float *X = b[0], *D = b[1], *G = b[2], *part = b[3];
+    RAPTOR_CK(hipMemcpyAsync(X, x, (size_t)12 * n, hipMemcpyHostToDevice, ctx->stream), "uploading inputs");
+    RAPTOR_CK(hipMemcpyAsync(D, dy, (size_t)8 * n, hipMemcpyHostToDevice, ctx->stream), "uploading inputs");
     if (form == RAPTOR_MLP_F32) {
-        RAPTOR_CK(hipMemsetAsync(G.p, 0, NP * 4, ctx->stream), "clearing gradients");
-        RAPTOR_CK(mlp_launch_backward_f32(S.P.p, X.p, D.p, n, G.p, ctx->stream), "launching the backward pass");
+        RAPTOR_CK(hipMemsetAsync(G, 0, NP * 4, ctx->stream), "clearing gradients");
+        RAPTOR_CK(mlp_launch_backward_f32(S.P.p, X, D, n, G, ctx->stream), "launching the backward pass");
     } else {
-        const int waves = (int)((n + 63) / 64);
-        DevBuf<float> part;
-        RAPTOR_CK(part.reserve((size_t)waves * NP), "allocating gradient partials");
-        RAPTOR_CK(mlp_launch_train(net_of(S), X.p, nullptr, D.p, 0, n, 1, 1.0f, part.p, nullptr, waves, ctx->stream),
+        RAPTOR_CK(mlp_launch_train(net_of(S), X, nullptr, D, 0, n, 1, 1.0f, part, nullptr, waves, ctx->stream),
                   "launching the backward pass");
-        RAPTOR_CK(mlp_launch_reduce(part.p, waves, 1, nullptr, nullptr, nullptr, 0, 0, 0, 0, 0, 1, 1, G.p, nullptr,
+        RAPTOR_CK(mlp_launch_reduce(part, waves, 1, nullptr, nullptr, nullptr, 0, 0, 0, 0, 0, 1, 1, G, nullptr,
                                     nullptr, nullptr, ctx->stream),
                   "reducing gradients");
-        RAPTOR_CK(hipStreamSynchronize(ctx->stream), "running the backward pass");
-        part.release();
     }
-    RAPTOR_CK(hipMemcpyAsync(dparams, G.p, NP * 4, hipMemcpyDeviceToHost, ctx->stream), "reading gradients");
+    RAPTOR_CK(hipMemcpyAsync(dparams, G, NP * 4, hipMemcpyDeviceToHost, ctx->stream), "reading gradients");
     RAPTOR_CK(hipStreamSynchronize(ctx->stream), "running the backward pass");
-    X.release();
-    D.release();
-    G.release();
     return RAPTOR_OK;
 }
 
@@ -390,32 +404,22 @@ raptor_status raptor_mlp_closure(raptor_ctx* ctx, int32_t form, const float* raw
         if (s != RAPTOR_OK) return s;
     }
     RAPTOR_CK(hipSetDevice(ctx->device), "selecting the device");
+    Scratch b(ctx, {(size_t)3 * n, exact ? (size_t)2 * n : 0, net ? (size_t)3 * n : 0, net ? (size_t)2 * n : 0});
+    RAPTOR_CK(b.error, "allocating inputs and outputs");
+    float *R = b[0], *E = b[1], *X = b[2], *Y = b[3];
+    hipStream_t st = ctx->stream;
+    RAPTOR_CK(hipMemcpyAsync(R, raw, (size_t)12 * n, hipMemcpyHostToDevice, st), "uploading inputs");
     if (exact) {
-        DevBuf<float> R, E;
-        RAPTOR_CK(R.reserve((size_t)3 * n), "allocating inputs");
-        RAPTOR_CK(E.reserve((size_t)2 * n), "allocating outputs");
-        RAPTOR_CK(hipMemcpyAsync(R.p, raw, (size_t)12 * n, hipMemcpyHostToDevice, ctx->stream), "uploading inputs");
-        RAPTOR_CK(mlp_launch_exact(ctx->k2t, n, R.p, E.p, ctx->stream), "launching the exact closure");
-        RAPTOR_CK(hipMemcpyAsync(exact, E.p, (size_t)8 * n, hipMemcpyDeviceToHost, ctx->stream), "reading outputs");
-        RAPTOR_CK(hipStreamSynchronize(ctx->stream), "running the exact closure");
-        R.release();
-        E.release();
+        RAPTOR_CK(mlp_launch_exact(ctx->k2t, n, R, E, st), "launching the exact closure");
+        RAPTOR_CK(hipMemcpyAsync(exact, E, (size_t)8 * n, hipMemcpyDeviceToHost, st), "reading outputs");
     }
     if (net) {
-        std::vector<float> x((size_t)3 * n), y((size_t)2 * n);
-        for (int64_t i = 0; i < n; ++i) {
-            x[3 * i] = mlp::norm_lx(raw[3 * i]);
-            x[3 * i + 1] = mlp::norm_lt(raw[3 * i + 1]);
-            x[3 * i + 2] = mlp::norm_cb(raw[3 * i + 2]);
-        }
-        raptor_status s = raptor_mlp_forward(ctx, form, x.data(), n, y.data());
-        if (s != RAPTOR_OK) return s;
-        for (int64_t i = 0; i < n; ++i) {
-            const double tc = mlp::cutoff_exponent(raw[3 * i], raw[3 * i + 1], raw[3 * i + 2]);
-            net[2 * i] = (float)(y[2 * i] * mlp::SIGMA_J + mlp::MU_J - tc);
-            net[2 * i + 1] = (float)(y[2 * i + 1] * mlp::SIGMA_A + mlp::MU_A - tc);
-        }
+        RAPTOR_CK(mlp_launch_net_inputs(R, n, X, st), "launching the network's inputs");
+        RAPTOR_CK(launch_net(ctx, form, X, n, Y), "launching the forward pass");
+        RAPTOR_CK(mlp_launch_net_outputs(R, n, Y, st), "launching the network's outputs");
+        RAPTOR_CK(hipMemcpyAsync(net, Y, (size_t)8 * n, hipMemcpyDeviceToHost, st), "reading outputs");
     }
+    RAPTOR_CK(hipStreamSynchronize(st), "running the closure");
     return RAPTOR_OK;
 }
 
