@@ -226,11 +226,13 @@ Geometry launch_geometry(const raptor_ctx* ctx, const raptor_plan& p, int n_nu, 
 
 // The work-groups of a launch: the plan's blocks_per_cu per compute unit, or as many as are resident
 // at once when 0 (a wave's LDS depends on the launch's rays per wave and its frequencies).  Tiles for
-// between one and two rounds of those go in two even rounds of fewer waves: 4096 tiles on 3072 waves
-// would leave two thirds of the chip's waves without work in the second (ms, 3072 and 2048 waves:
-// 256^2 at 16 rays, one frequency 3.79 3.10, 24 frequencies 6.56 5.73; 512 x 256 at 32 rays 4.70 3.90;
-// 512^2 at 64 rays 6.35 5.51).  From two rounds on it is no gain (8192 tiles in three rounds: 512^2 at
-// 32 rays 5.37 5.82, 512 x 256 at 16 rays and 24 frequencies 7.53 8.50).
+// 1.1 to two rounds of those go in two even rounds of fewer waves: 4096 tiles on 3072 waves would
+// leave two thirds of the chip's waves without work in the second (ms, 3072 and 2048 waves: 256^2 at
+// 16 rays, one frequency 3.79 3.10, 24 frequencies 6.56 5.73; 512 x 256 at 32 rays 4.70 3.90; 512^2 at
+// 64 rays 6.35 5.51; 1.15 rounds, 240 x 236 3.25 3.07, 476^2 5.72 5.29).  With fewer tiles over the
+// first round they end beside its longest rays (1.04 rounds, 226^2 2.94 3.16, 452^2 4.55 4.84), and
+// from two rounds on it is no gain (8192 tiles in three rounds: 512^2 at 32 rays 5.37 5.82, 512 x 256
+// at 16 rays and 24 frequencies 7.53 8.50).
 int launch_blocks(const raptor_ctx* ctx, const LaunchPlan& pl, int n_nu, bool mlpc, int integ, int rays,
                   long long tiles)
 {
@@ -241,7 +243,7 @@ int launch_blocks(const raptor_ctx* ctx, const LaunchPlan& pl, int n_nu, bool ml
         per_cu = std::max(1, std::min(pl.resident, (int)fit));
         const int waves = pl.p.threads / 64;
         const long long all = (long long)ctx->cu_count * per_cu, need = (tiles + waves - 1) / waves;
-        if (need > all && need < 2 * all) return (int)((need + 1) / 2);
+        if (10 * need >= 11 * all && need < 2 * all) return (int)((need + 1) / 2);
     }
     return ctx->cu_count * per_cu;
 }
