@@ -203,11 +203,17 @@ int most_rays(int n_nu, bool mlpc, bool cutoff)
 // frequencies, 256^2: 9.98 7.81 5.38 5.76 8.29; but 6 frequencies, 2 x 480 x 400: 9.69 10.7 13.2), the
 // learned closure's for 32 too (200^2: 9.11 5.80 3.76 4.79 5.70), at four times for both together (4
 // frequencies, 4 x 256^2: 40.1 33.0 29.5 34.1).
-Geometry launch_geometry(const raptor_ctx* ctx, const raptor_plan& p, int n_nu, bool mlpc, int integ, bool cutoff,
+Geometry launch_geometry(const raptor_ctx* ctx, const raptor_plan& p, int n_nu, bool mlpc, const raptor_opts* o,
                          const JobIn* in, int nj)
 {
-    Geometry g = plan_geometry(p, n_nu, mlpc, integ);
+    Geometry g = plan_geometry(p, n_nu, mlpc, o->integrator);
     if (g.rays < 64) return g;
+    // The optical-depth-aware step has a round for every step whatever the wave's rays: as many as can
+    // share it (ms, the fewer rays below and 64: one frequency, 64^2 57.8 49.1, 512^2 65.8 51.1; 256^2, 4
+    // frequencies 90.6 79.6, 24 frequencies 332 280).
+    if (o->tau_step > 0.0 && !mlpc &&
+        trace_kernel_lds(n_nu, p.min_waves_per_simd, p.threads, mlpc, o->integrator, 64) <= ctx->lds_per_block)
+        return g;
     long long n = 0;
     for (int k = 0; k < nj; ++k) n += (long long)in[k].cam->nx * in[k].cam->ny;
     const long long simds = 4ll * ctx->cu_count;
@@ -219,7 +225,7 @@ Geometry launch_geometry(const raptor_ctx* ctx, const raptor_plan& p, int n_nu, 
            : n <= simds * 192     ? 32    // 6 (the resident 64-ray tiles)
            : n > simds * 240 && n < simds * 336 ? 32
                                   : 64;
-    g.rays = std::min(g.rays, most_rays(n_nu, mlpc, cutoff));
+    g.rays = std::min(g.rays, most_rays(n_nu, mlpc, o->tau_cutoff > 0.0));
     if (g.tile_w > g.rays) g.tile_w = g.rays;
     return g;
 }
@@ -601,7 +607,7 @@ raptor_status run_jobs(raptor_ctx* ctx, const JobIn* in, int nj, int n_nu, const
     std::vector<const raptor_grid*> gl(nj);
     std::vector<double> nus((size_t)nj * n_nu), pixsr(nj);
     HostTables h{jobs.data(), grids.data(), gl.data(), nus.data(), pixsr.data()};
-    const Geometry geo = launch_geometry(ctx, plan.p, n_nu, mlpc, o->integrator, o->tau_cutoff > 0.0, in, nj);
+    const Geometry geo = launch_geometry(ctx, plan.p, n_nu, mlpc, o, in, nj);
     raptor_status fs = fill_tables(ctx, in, nj, n_nu, o, geo.tile_w, geo.rays, &h);
     if (fs != RAPTOR_OK) return fs;
 
@@ -992,7 +998,7 @@ raptor_status raptor_trace_batch_noalloc(raptor_ctx* ctx, const raptor_camera* c
     if ((s = plan_for(ctx, n_nu, fp32, &plan, opts->closure >= RAPTOR_CLOSURE_MLP, false)) != RAPTOR_OK) return s;
     HostTables h{na.jobs, na.grids, na.gl, na.nus, na.pixsr};
     const Geometry geo =
-        launch_geometry(ctx, plan.p, n_nu, opts->closure >= RAPTOR_CLOSURE_MLP, opts->integrator, opts->tau_cutoff > 0.0, na.in, n_cams);
+        launch_geometry(ctx, plan.p, n_nu, opts->closure >= RAPTOR_CLOSURE_MLP, opts, na.in, n_cams);
     if ((s = fill_tables(ctx, na.in, n_cams, n_nu, opts, geo.tile_w, geo.rays, &h)) != RAPTOR_OK) return s;
     // the launch's buffers, carved from the scratch in 256-byte aligned regions
     unsigned char* base = static_cast<unsigned char*>(ctx->noalloc_scratch);
