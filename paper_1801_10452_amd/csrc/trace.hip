@@ -264,13 +264,15 @@ __device__ inline float attenuation<float>(double tau) { return rt::exp_mixed(-t
 // ---------------------------------------------------------------------------------------
 constexpr int N_FIELDS = 10;   // t, r, theta, phi, k^t, k^r, k^phi, sin, cos, |dlambda|
 constexpr int F_DL = 9;
-// A sample record: the ten fields, then a word with the owner's lane (byte 0) and the slot of the
-// owner's next sample (byte 1), and the step number of the sample.  Eleven doubles: an odd stride
-// lets consecutive lanes access consecutive records without bank conflicts.  After the evaluation
-// the fields hold its results: contributions in [0, FREQ_GROUP), optical depths behind them (the
-// step length stays).
+// A sample record: the ten fields, then a word with the owner's lane (byte 0, with DROPPED once the
+// cut-off has stopped the ray before this sample), the slot of the owner's next sample (byte 1) and
+// the ray's pole crossings so far (byte 2, modulo 256), and the step number of the sample.  Eleven
+// doubles: an odd stride lets consecutive lanes access consecutive records without bank conflicts.
+// After the evaluation the fields hold its results: contributions in [0, FREQ_GROUP), optical depths
+// behind them (the step length stays).
 constexpr int REC = 11;
 constexpr int REC_LINK = 80, REC_STEP = 84;   // byte offsets
+constexpr unsigned char DROPPED = 128;
 
 // Frequencies evaluated together (independent dependency chains) by one lane.
 constexpr int FREQ_GROUP = 4;
@@ -426,17 +428,17 @@ struct MlpSample {
         nus = (2.0 / 9.0) * nuc * fl[1] * fl[1] * ::sqrt(::fmax(1.0 - cb * cb, 0.0));
         return zamo;
     }
+    // fallback, dropped: whether the exact closure took the sample, and whether it was skipped
     __device__ inline void contribution(const TraceParams& p, const unsigned char* lds_net, double nu_obs, double& A,
-                                        double& dtau, unsigned long long& c_fallback, unsigned long long& c_dropped)
+                                        double& dtau, bool& fallback, bool& dropped)
     {
         const double nu = has ? nu_obs * nr : nuc;
         const float lx = (float)rt::log_pos(nu / nuc);
         const bool inb = has && tr.emits && mlp::in_box(lx, lth, (float)cb);
         // X^1/3 + ln K2 > MLP_ZERO_EXP  <=>  X > t_lim^3, t_lim = MLP_ZERO_EXP - ln K2 (X^1/3 >= 0)
         const double t_lim = MLP_ZERO_EXP - tr.ln_k2;
-        const bool drop = has && tr.emits && !inb && (t_lim <= 0.0 || nu > t_lim * t_lim * t_lim * nus);
-        c_fallback += __popcll(__ballot(has && tr.emits && !inb && !drop));
-        c_dropped += __popcll(__ballot(drop));
+        dropped = has && tr.emits && !inb && (t_lim <= 0.0 || nu > t_lim * t_lim * t_lim * nus);
+        fallback = has && tr.emits && !inb && !dropped;
         const float x0 = inb ? mlp::norm_lx(lx) : 0.0f, x1 = inb ? mlp::norm_lt(lth) : 0.0f,
                     x2 = inb ? mlp::norm_cb((float)cb) : 0.0f;
         float y0, y1;
@@ -463,7 +465,7 @@ struct MlpSample {
                 const double al = ne * pl::J_PREF / (2.0 * pl::ME_CGS * nuc) * ::exp(lna) * planck;
                 pl::step_source(j, al, j / al, ds, inr3, A, dtau);
             }
-        } else if (tr.emits && !drop) {
+        } else if (fallback) {
             tr.contribution(p, nu_obs, A, dtau);
         }
     }
@@ -513,11 +515,12 @@ trace_kernel(TraceParams args)
     bool have_acc = false;
     double a = 0.0, r_stop = 0.0, r_esc = 0.0, sth = 0.0, cth = 1.0;
     int steps = 0;
-    // this ray's queued samples: oldest slot in bits 0-7, newest in 8-15, their number above
+    // this ray's queued samples: oldest slot in bits 0-7, newest in 8-15, their number in 16-23; in
+    // 24-31 the pole crossings of the lane's rays, modulo 256
     unsigned queued = 0;
     int lead = NNU > FREQ_GROUP ? (p.n_nu - 1) / G * G : 0;   // cut-off: the group looked at first in a round
     const auto first = [&] { return (int)(queued & 255u); };
-    const auto pending = [&] { return (int)(queued >> 16); };
+    const auto pending = [&] { return (int)(queued >> 16 & 255u); };
     int status = RAY_IDLE;
     // the ray's accumulated intensities and optical depths (doubles; the per-sample terms are TT),
     // and d tau / d|lambda| of its last sample at the most absorbing frequency (optical-depth-aware
@@ -691,7 +694,10 @@ trace_kernel(TraceParams args)
         if (!hold) c_steps += __popcll(run);
         const unsigned long long events = __ballot(event);
         if (events) {
-            if (reflected) atomicAdd(tally, 1u);
+            if (reflected) {
+                atomicAdd(tally, 1u);
+                queued += 1u << 24;
+            }
             const unsigned long long ended = __ballot(status > RAY_RUNNING) & run;
             run &= ~ended;
             wait |= ended;
@@ -709,12 +715,13 @@ trace_kernel(TraceParams args)
             const int lane = fresh(threadIdx.x & 63);
             double* my_row = row_of(lane);
             const int n_eval = total < 64 ? total : 64;
-            const bool has = lane < n_eval;
-            int slot = head + (has ? lane : 0);
+            int slot = head + (lane < n_eval ? lane : 0);
             slot = slot >= SLOTS ? slot - SLOTS : slot;
             double* rec = ring + slot * REC;
             // (a lane without a sample reads the oldest one's owner: a lane with a job)
-            const int owner = link_of(ring, slot)[0];
+            const unsigned char link = link_of(ring, slot)[0];
+            const int owner = link & 63;
+            const bool has = lane < n_eval && !(link & DROPPED);
             double q[N_FIELDS];
 #pragma unroll
             for (int f = 0; f < N_FIELDS; ++f) q[f] = MLPC && !has ? 1.0 : rec[f];
@@ -731,7 +738,7 @@ trace_kernel(TraceParams args)
                 nu_base = li.nu_base;
                 zamo = setup_sample<TT>(p, q, li, tr);
             }
-            c_zamo += __popcll(__ballot(zamo));
+            int fallback = 0, dropped = 0;   // of this lane's sample, over the frequencies folded
 
             // whether slot s lies among the evaluated samples
             auto evaluated = [&](int s) {
@@ -761,19 +768,25 @@ trace_kernel(TraceParams args)
             for (int k = 0, f0 = groups && p.tau_step == 0.0 ? lead : 0; k < p.n_nu;) {
                 const int cnt = p.n_nu - f0;
                 double A[G], dt[G];
+                int group_fb = 0, group_dr = 0;
 #pragma unroll
                 for (int g = 0; g < G; ++g) {
                     A[g] = 0.0;
                     dt[g] = 0.0;
                 }
                 if (MLPC) {
+                    bool fb, dr;
                     if (NNU == 1) {
-                        ms.contribution(p, lds_net, p.nu[nu_base], A[0], dt[0], c_fallback, c_dropped);
+                        ms.contribution(p, lds_net, p.nu[nu_base], A[0], dt[0], fb, dr);
+                        group_fb = fb;
+                        group_dr = dr;
                     } else {
 #pragma unroll 1
                         for (int g = 0; g < G && g < cnt; ++g) {
                             double Ag, dg;
-                            ms.contribution(p, lds_net, p.nu[nu_base + f0 + g], Ag, dg, c_fallback, c_dropped);
+                            ms.contribution(p, lds_net, p.nu[nu_base + f0 + g], Ag, dg, fb, dr);
+                            group_fb += fb;
+                            group_dr += dr;
 #pragma unroll
                             for (int k = 0; k < G; ++k) {
                                 A[k] = k == g ? Ag : A[k];
@@ -834,12 +847,14 @@ trace_kernel(TraceParams args)
                         continue;
                     }
                 }
+                fallback += group_fb;
+                dropped += group_dr;
                 if (spread) {
                     const int j = lane / G, g = lane % G;
                     const bool on = j < n_rays && g < cnt;
                     const int o = on ? ray_tab[j] : 0;
                     const unsigned oq = __shfl(queued, o, 64);
-                    int s = (int)(oq & 255u), left = (int)(oq >> 16);
+                    int s = (int)(oq & 255u), left = (int)(oq >> 16 & 255u);
                     double* row = rows + o * ROW + f0 + g;
                     double It = 0.0, t0 = 0.0;
                     if (on) {
@@ -876,7 +891,6 @@ trace_kernel(TraceParams args)
                     taken = 0;
                     bool more = mine;
                     while (__ballot(more)) {
-                        if (one_lane && f0 == 0) c_samples += __popcll(__ballot(more));
                         if (more) {
                             const int s = nxt;
                             const double* r = ring + s * REC;
@@ -915,17 +929,40 @@ trace_kernel(TraceParams args)
                 k += G;
                 f0 = f0 + G < p.n_nu ? f0 + G : 0;
             }
-            // each ray leaves the folded samples behind; one found opaque stops at that sample
-            if (!one_lane) c_samples += n_eval;
+            // each ray leaves the folded samples behind; one found opaque stops at that sample: its
+            // later ones are dropped, and the counters hold what it took up to there
             if (mine) {
                 const int left = spread ? ray_left[lane] : pending() - taken;
-                queued = (queued & 0xff00u) | ((unsigned)left << 16) | (unsigned)(spread ? ray_next[lane] : nxt);
+                queued = (queued & 0xff00ff00u) | ((unsigned)left << 16) | (unsigned)(spread ? ray_next[lane] : nxt);
                 if (stop >= 0) {
-                    const int at = *reinterpret_cast<const int*>(link_of(ring, stop) + REC_STEP - REC_LINK);
+                    const unsigned char* l = link_of(ring, stop);
+                    const int at = *reinterpret_cast<const int*>(l + REC_STEP - REC_LINK);
                     atomicAdd(p.stats + ST_STEPS, (unsigned long long)(at - steps));   // steps beyond the stop
+                    atomicSub(tally, (queued >> 24) - l[2] & 255u);                    // crossings beyond it
+                    for (int s = nxt, n = left; n > 0; --n) {
+                        unsigned char* d = link_of(ring, s);
+                        *d |= DROPPED;
+                        s = d[1];
+                    }
                     status = RAY_OPAQUE;
                     steps = at;
-                    queued = 0;
+                    queued &= 0xff000000u;
+                }
+            }
+            bool folded = has;
+            if (p.tau_cutoff > 0.0) {
+                wave_lds_sync();
+                folded = has && !(link_of(ring, slot)[0] & DROPPED);
+                c_samples += __popcll(__ballot(folded));
+            } else {
+                c_samples += n_eval;
+            }
+            c_zamo += __popcll(__ballot(folded && zamo));
+            if (MLPC) {
+#pragma unroll
+                for (int b = 0; 1 << b <= NNU; ++b) {
+                    c_fallback += (unsigned long long)__popcll(__ballot(folded && (fallback >> b & 1))) << b;
+                    c_dropped += (unsigned long long)__popcll(__ballot(folded && (dropped >> b & 1))) << b;
                 }
             }
             if (p.tau_cutoff > 0.0) {
@@ -957,12 +994,12 @@ trace_kernel(TraceParams args)
             rec[8] = cth;
             rec[F_DL] = row_of(lane)[RATE];
             unsigned char* l = link_of(ring, s);
-            *reinterpret_cast<int*>(l) = lane;
+            *reinterpret_cast<int*>(l) = lane | (int)(queued >> 8 & 0xff0000u);
             *reinterpret_cast<int*>(l + REC_STEP - REC_LINK) = steps;
             if (pending() > 0)
                 link_of(ring, (int)((queued >> 8) & 255u))[1] = (unsigned char)s;
             else
-                queued = (unsigned)s;
+                queued = (queued & 0xff000000u) | (unsigned)s;
             queued = ((queued + 0x10000u) & ~0xff00u) | ((unsigned)s << 8);
         }
         total += __popcll(adds);
