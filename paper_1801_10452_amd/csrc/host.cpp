@@ -208,15 +208,20 @@ Geometry launch_geometry(const raptor_ctx* ctx, const raptor_plan& p, int n_nu, 
 {
     Geometry g = plan_geometry(p, n_nu, mlpc, o->integrator);
     if (g.rays < 64) return g;
-    // The optical-depth-aware step has a round for every step whatever the wave's rays: as many as can
-    // share it (ms, the fewer rays below and 64: one frequency, 64^2 57.8 49.1, 512^2 65.8 51.1; 256^2, 4
-    // frequencies 90.6 79.6, 24 frequencies 332 280).
-    if (o->tau_step > 0.0 && !mlpc &&
-        trace_kernel_lds(n_nu, p.min_waves_per_simd, p.threads, mlpc, o->integrator, 64) <= ctx->lds_per_block)
-        return g;
     long long n = 0;
     for (int k = 0; k < nj; ++k) n += (long long)in[k].cam->nx * in[k].cam->ny;
     const long long simds = 4ll * ctx->cu_count;
+    // The optical-depth-aware step has a round at every step, whose samples share the wave's lanes by
+    // frequency.  With many frequencies 32 rays leave fewer lanes idle, and take half the LDS; with few
+    // the lanes of the step itself count (ms at 64 and 32 rays, FP32 and FP64 transfer: four frequencies
+    // 256^2 5.1 5.3 and 6.5 6.1, 400^2 5.9 7.2 and 7.5 8.3; 6, 256^2 56 49 and 84 63; 8, 512^2 61 69 and
+    // 99 94, 6 x 512^2 124 144 and 173 176; 12, 400^2 100 58 and 162 87, 6 x 512^2 133 163 and 226 200;
+    // 24, 256^2 105 72 and 215 128, 6 x 512^2 238 197 and 482 312).
+    if (o->tau_step > 0.0 && !mlpc) {
+        if (n_nu > 16 || (n_nu > 4 && n <= simds * 192)) g.rays = 32;
+        if (g.tile_w > g.rays) g.tile_w = g.rays;
+        return g;
+    }
     const long long few = n / (mlpc && n_nu > 1 ? 4 : mlpc || n_nu > 4 ? 2 : 1);
     if (mlpc) n = few;
     g.rays = few <= simds * 6     ? 4     // up to 1.5 tiles of the size per SIMD
@@ -239,15 +244,18 @@ Geometry launch_geometry(const raptor_ctx* ctx, const raptor_plan& p, int n_nu, 
 // first round they end beside its longest rays (1.04 rounds, 226^2 2.94 3.16, 452^2 4.55 4.84), and
 // from two rounds on it is no gain (8192 tiles in three rounds: 512^2 at 32 rays 5.37 5.82, 512 x 256
 // at 16 rays and 24 frequencies 7.53 8.50).
-int launch_blocks(const raptor_ctx* ctx, const LaunchPlan& pl, int n_nu, bool mlpc, int integ, int rays,
+int launch_blocks(const raptor_ctx* ctx, const LaunchPlan& pl, int n_nu, bool mlpc, int integ, int rays, bool each,
                   long long tiles)
 {
     int per_cu = pl.p.blocks_per_cu;
     if (per_cu == 0) {
-        const size_t lds = trace_kernel_lds(n_nu, pl.p.min_waves_per_simd, pl.p.threads, mlpc, integ, rays);
+        const size_t lds = trace_kernel_lds(n_nu, pl.p.min_waves_per_simd, pl.p.threads, mlpc, integ, rays, each);
         const size_t fit = LDS_BYTES / ((lds + LDS_GRANULE - 1) / LDS_GRANULE * LDS_GRANULE);
-        per_cu = std::max(1, std::min(pl.resident, (int)fit));
         const int waves = pl.p.threads / 64;
+        int held = pl.resident;
+        // (the plan's figure is of the ring's kernels: two waves per SIMD here)
+        if (each && kernel_wpe(pl.p.min_waves_per_simd, mlpc, integ, true) < 3) held = std::min(held, 8 / waves);
+        per_cu = std::max(1, std::min(held, (int)fit));
         const long long all = (long long)ctx->cu_count * per_cu, need = (tiles + waves - 1) / waves;
         if (10 * need >= 11 * all && need < 2 * all) return (int)((need + 1) / 2);
     }
@@ -496,7 +504,8 @@ raptor_status launch_tables(raptor_ctx* ctx, const HostTables& h, const DevTable
     const bool fp32 = o->transfer_prec == RAPTOR_F32;
     const bool mlpc = o->closure >= RAPTOR_CLOSURE_MLP;
     const int rays_shift = log2_of(geo.rays);
-    const int blocks = launch_blocks(ctx, plan, n_nu, mlpc, o->integrator, geo.rays, h.tiles);
+    const bool each = o->tau_step > 0.0;
+    const int blocks = launch_blocks(ctx, plan, n_nu, mlpc, o->integrator, geo.rays, each, h.tiles);
     hipStream_t s = ctx->stream;
     RAPTOR_CK(hipMemcpyAsync(d.jobs, h.jobs, nj * sizeof(DevJob), hipMemcpyHostToDevice, s), "uploading jobs");
     RAPTOR_CK(hipMemcpyAsync(d.grids, h.grids, h.n_grids * sizeof(DevGrid), hipMemcpyHostToDevice, s),
@@ -538,7 +547,7 @@ raptor_status launch_tables(raptor_ctx* ctx, const HostTables& h, const DevTable
     p.rays_per_wave = geo.rays;
     p.rays_shift = rays_shift;
     p.n_nu = n_nu;
-    p.slots = trace_kernel_slots(n_nu, plan.p.min_waves_per_simd, mlpc, o->integrator, geo.rays);
+    p.slots = trace_kernel_slots(n_nu, plan.p.min_waves_per_simd, mlpc, o->integrator, geo.rays, each);
     p.r_in = h.grids[0].r_in;
     p.r_out = h.grids[0].r_out;
     for (int i = 1; i < h.n_grids; ++i)

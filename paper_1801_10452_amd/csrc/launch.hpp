@@ -20,18 +20,20 @@ hipError_t trace_kernel_attributes(int max_nu, bool fp32, int wpe, bool mlpc, in
                                    int* spill_bytes, int* max_threads);
 // mlpc: the variant with the learned closure; integ: INTEG_* (the second-order integrators have
 // the 2- and 3-waves-per-SIMD variants; a request for 1 takes 2)
-const void* trace_kernel_symbol(int max_nu, bool fp32, int wpe, bool mlpc = false, int integ = INTEG_RK4);
+// each: the kernels of the optical-depth-aware step, which evaluate each sample after its step
+const void* trace_kernel_symbol(int max_nu, bool fp32, int wpe, bool mlpc = false, int integ = INTEG_RK4,
+                                bool each = false);
 // A compute unit's LDS, and the granules it is handed out in.
 constexpr size_t LDS_BYTES = 163840, LDS_GRANULE = 1280;
 // Dynamic LDS bytes of a trace launch's work-group of `threads` lanes (mlpc: plus the staged network);
-// the same (wpe, mlpc, integ) select the instantiation in trace_kernel_symbol, whose queue this sizes.
-size_t trace_kernel_lds(int n_nu, int wpe, int threads, bool mlpc, int integ, int rays);
-// sample-ring slots of a wave in that LDS
-int trace_kernel_slots(int n_nu, int wpe, bool mlpc, int integ, int rays);
+// the same (wpe, mlpc, integ, each) select the instantiation in trace_kernel_symbol, whose queue this sizes.
+size_t trace_kernel_lds(int n_nu, int wpe, int threads, bool mlpc, int integ, int rays, bool each = false);
+// sample records of a wave in that LDS
+int trace_kernel_slots(int n_nu, int wpe, bool mlpc, int integ, int rays, bool each);
 // whether a plan may ask for fewer than 64 rays per wave in this class (raptor_plan)
 bool trace_plan_takes_rays(int max_nu, int wpe, bool mlpc, int integ);
 // Waves-per-SIMD variant actually instantiated for a requested one.
-int kernel_wpe(int wpe, bool mlpc, int integ);
+int kernel_wpe(int wpe, bool mlpc, int integ, bool each);
 
 // ---- thin disk (disk.hip)
 constexpr int DISK_THREADS = 64;

@@ -61,6 +61,19 @@ struct Transfer<double> {
     double ne, the, bf, sinb, ln_k2, ds, inr3, nr;
     bool emits;
     bool live;   // the sample contributes (a positive fluid-frame frequency)
+    // the state as doubles: a record's words while several lanes share its sample
+    static constexpr int WORDS = 9;
+    __device__ inline void to_words(double* w) const
+    {
+        w[0] = ne; w[1] = the; w[2] = bf; w[3] = sinb; w[4] = ln_k2; w[5] = ds; w[6] = inr3; w[7] = nr;
+        w[8] = __hiloint2double((int)live, (int)emits);
+    }
+    __device__ inline void from_words(const double* w)
+    {
+        ne = w[0]; the = w[1]; bf = w[2]; sinb = w[3]; ln_k2 = w[4]; ds = w[5]; inr3 = w[6]; nr = w[7];
+        emits = __double2loint(w[8]) != 0;
+        live = __double2hiint(w[8]) != 0;
+    }
     __device__ inline void setup(const TraceParams& p, const double fl[4], double nr_, double cosb, double dsv)
     {
         ne = fl[0]; the = fl[1]; bf = fl[2];
@@ -118,6 +131,26 @@ struct Transfer<float> {
     double nr;
     bool emits;
     bool live;   // the sample contributes (a positive fluid-frame frequency)
+    static constexpr int WORDS = 7;
+    __device__ static inline double pack(float a, float b)
+    {
+        return __hiloint2double((int)__float_as_uint(b), (int)__float_as_uint(a));
+    }
+    __device__ inline void to_words(double* w) const
+    {
+        w[0] = pack(ne, the); w[1] = pack(inv_the, nu_s); w[2] = pack(ds, inr3);
+        w[3] = ln_k2; w[4] = nr_inv_nus; w[5] = nr;
+        w[6] = __hiloint2double((int)live, (int)emits);
+    }
+    __device__ inline void from_words(const double* w)
+    {
+        ne = __uint_as_float((unsigned)__double2loint(w[0])); the = __uint_as_float((unsigned)__double2hiint(w[0]));
+        inv_the = __uint_as_float((unsigned)__double2loint(w[1])); nu_s = __uint_as_float((unsigned)__double2hiint(w[1]));
+        ds = __uint_as_float((unsigned)__double2loint(w[2])); inr3 = __uint_as_float((unsigned)__double2hiint(w[2]));
+        ln_k2 = w[3]; nr_inv_nus = w[4]; nr = w[5];
+        emits = __double2loint(w[6]) != 0;
+        live = __double2hiint(w[6]) != 0;
+    }
     __device__ inline void setup(const TraceParams& p, const double fl[4], double nr_, double cosb, double dsv)
     {
         ne = (float)fl[0];
@@ -250,12 +283,14 @@ __device__ inline float attenuation<float>(double tau) { return rt::exp_mixed(-t
 // whichever lanes the samples come from.  Once 64 are queued the wave evaluates the oldest 64
 // together, one per lane, so the expensive part (MKS map, gather, fluid frame, closure) runs on
 // full waves; it evaluates fewer only when the next step's samples would not fit, when no ray is
-// left running, when as many rays wait for their last samples as still run, or when the run needs
-// each sample before the ray goes on (optical-depth-aware step; the optical-depth cut-off limits
-// how many samples a ray may have waiting).  The samples of a ray are chained through their
-// records; after a round each ray folds its evaluated samples into (I, tau) in the order they were
-// taken, which keeps the backward transfer identical to evaluating every sample right after its
+// left running, when as many rays wait for their last samples as still run, or when a ray has as many
+// samples waiting as the optical-depth cut-off allows.  The samples of a ray are chained through
+// their records; after a round each ray folds its evaluated samples into (I, tau) in the order they
+// were taken, which keeps the backward transfer identical to evaluating every sample right after its
 // step.  A ray that has ended waits in its lane until its samples are folded.
+//
+// The optical-depth-aware step needs each sample before its ray goes on: its kernels (EACH) queue
+// nothing and evaluate and fold the samples of a step at once, one per ray.
 //
 // A ring shared by the wave, against a queue of K samples per lane (K = 1 to 3) whose first full
 // lane forced a round: a lone long ray at the end of a wave's work has a round every 64 of its
@@ -279,6 +314,8 @@ constexpr int FREQ_GROUP = 4;
 // Cut-off: samples a ray may have waiting (those behind the one that makes it opaque are dropped).
 constexpr int CUT_PENDING = 8;
 static_assert(2 * FREQ_GROUP <= F_DL, "the results of a group fit the record below the step length");
+static_assert(Transfer<double>::WORDS <= F_DL && Transfer<float>::WORDS <= F_DL,
+              "the transfer set-up fits the record below the step length");
 
 // What the evaluation of a queued sample needs from its ray's job.
 struct LaneInfo {
@@ -329,10 +366,8 @@ __device__ inline void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ inline unsigned char* link_of(double* ring, int slot)
-{
-    return reinterpret_cast<unsigned char*>(ring + slot * REC) + REC_LINK;
-}
+__device__ inline unsigned char* link_of(double* rec) { return reinterpret_cast<unsigned char*>(rec) + REC_LINK; }
+__device__ inline unsigned char* link_of(double* ring, int slot) { return link_of(ring + slot * REC); }
 
 // The frequency-independent part of a queued sample's evaluation: fluid state, fluid frame and
 // the transfer set-up.  A sample whose fluid-frame frequency is not positive (integration error
@@ -474,7 +509,7 @@ struct MlpSample {
 // Work-groups of up to 256 lanes; up to 512 for the learned closure's 2-waves-per-SIMD variant,
 // whose eight waves share one LDS copy of the network (a 512-lane group caps a kernel at 256
 // registers per lane, which that variant fits anyway).
-template <int NNU, class TT, int WPE, bool MLPC, int INTEG>
+template <int NNU, class TT, int WPE, bool MLPC, int INTEG, bool EACH>
 __global__ void __attribute__((amdgpu_flat_work_group_size(64, (MLPC && WPE >= 2) ? 512 : 256),
                                amdgpu_waves_per_eu(WPE, 8)))
 trace_kernel(TraceParams args)
@@ -523,9 +558,9 @@ trace_kernel(TraceParams args)
     const auto pending = [&] { return (int)(queued >> 16 & 255u); };
     int status = RAY_IDLE;
     // the ray's accumulated intensities and optical depths (doubles; the per-sample terms are TT),
-    // and d tau / d|lambda| of its last sample at the most absorbing frequency (optical-depth-aware
-    // step; 0: no transfer limit on the next step).  Between a step and the queueing of its sample
-    // the last word holds the step length.
+    // and a last word: the step length between a step and the queueing of its sample, and with EACH,
+    // from the sample to the next step, d tau / d|lambda| of the sample at its most absorbing frequency
+    // (0: no transfer limit on the next step).
     const int RATE = 2 * COLS;
     // this lane's row (for the lanes below RAYS); as the other per-lane LDS addresses formed where it
     // is used, from `fresh(lane)`, so that no register holds it across the step
@@ -622,15 +657,13 @@ trace_kernel(TraceParams args)
             }
         }
         if ((run | (unsigned long long)total) == 0ull) break;   // nothing running or queued: the tiles are drained
-        // with the optical-depth-aware step the queued samples are folded before the next step
-        const bool hold = p.tau_step > 0.0 && total > 0;
 
         // ------------------------------------------------------------ one step of every running ray
         bool event = false, reflected = false, want = false;
-        if (__builtin_amdgcn_inverse_ballot_w64(hold ? 0ull : run)) {
+        if (__builtin_amdgcn_inverse_ballot_w64(run)) {
             const rk::Spin<double> sp = rk::make_spin(a, M);
             double h = rk::step_size(p.eps, y);
-            if (p.tau_step > 0.0) {
+            if constexpr (EACH) {
                 double* my_row = row_of(fresh(lane));
                 const double rate = my_row[RATE];
                 if (rate > 0.0) h = ::fmin(h, p.tau_step / rate);
@@ -691,7 +724,7 @@ trace_kernel(TraceParams args)
                 if (want) row_of(fresh(lane))[RATE] = h;
             }
         }
-        if (!hold) c_steps += __popcll(run);
+        c_steps += __popcll(run);
         const unsigned long long events = __ballot(event);
         if (events) {
             if (reflected) {
@@ -703,14 +736,160 @@ trace_kernel(TraceParams args)
             wait |= ended;
         }
 
-        // ------------------------------------------------------------ evaluate queued samples
         unsigned long long adds = __ballot(want);
         const int n_want = __popcll(adds);
-        bool round = total >= 64 || total + n_want > SLOTS || hold;
-        if (!round && total > 0)
+        // this ray's sample into its record, with the lane and the pole crossings
+        const auto put = [&](double* rec, int lane) {
+            rec[0] = y[0];
+            rec[1] = y[1];
+            rec[2] = y[2];
+            rec[3] = y[3];
+            rec[4] = y[4];
+            rec[5] = y[5];
+            rec[6] = y[7];
+            rec[7] = sth;
+            rec[8] = cth;
+            rec[F_DL] = row_of(lane)[RATE];
+            *reinterpret_cast<int*>(rec + N_FIELDS) = lane | (int)(queued >> 8 & 0xff0000u);
+        };
+
+        // ------------------------------------------------------------ evaluate and fold the step's samples
+        if (EACH && adds) {
+            // One sample per ray.  Lane i sets up sample i and leaves the set-up in its record; then
+            // `per` consecutive lanes share each sample, lane c of them taking its frequencies
+            // [c m, (c + 1) m), m = ceil(n_nu / per): contribution and fold, I += exp(-tau) A, tau +=
+            // dtau, straight into the owner's row.  (As rounds of the ring, a group of frequencies
+            // after another on the lanes with a sample, 256^2 at 4 and 24 frequencies took 79.6 and
+            // 280 ms against 68 and 207, FP64 transfer, and with the cut-off, whose groups are looked
+            // at before they are folded, 81 and 478 against 66 and 192.)
+            const TraceParams& p = fresh_params();
+            const int lane = fresh(threadIdx.x & 63);
+            double* my_rec = ring + lane_rank(adds) * REC;
+            if (__builtin_amdgcn_inverse_ballot_w64(adds)) put(my_rec, lane);
+            wave_lds_sync();
+            const bool has = lane < n_want;
+            double* rec = ring + (has ? lane : 0) * REC;
+            const int owner = link_of(rec)[0];
+            const LaneInfo li = lane_info(p, lane_job[owner]);
+            double q[N_FIELDS];
+#pragma unroll
+            for (int f = 0; f < N_FIELDS; ++f) q[f] = MLPC && !has ? 1.0 : rec[f];
+            double* row = rows + owner * ROW;
+            double tmin = 1e300, dmax = 0.0;   // over the frequencies of this lane
+            const auto fold = [&](int f, double t0, TT att, double A, double dt) {
+                row[f] = __builtin_fma((double)att, A, row[f]);
+                const double t1 = t0 + dt;
+                row[COLS + f] = t1;
+                tmin = ::fmin(tmin, t1);
+                dmax = ::fmax(dmax, dt);
+            };
+            if (MLPC) {
+                MlpSample<TT> ms;
+                c_zamo += __popcll(__ballot(ms.setup(p, has, q, li)));
+#pragma unroll 1
+                for (int f = 0; f < p.n_nu; ++f) {
+                    double A, dt;
+                    bool fb, dr;
+                    ms.contribution(p, lds_net, p.nu[li.nu_base + f], A, dt, fb, dr);
+                    c_fallback += __popcll(__ballot(fb));
+                    c_dropped += __popcll(__ballot(dr));
+                    if (has) {
+                        const double t0 = row[COLS + f];
+                        fold(f, t0, attenuation<TT>(t0), A, dt);
+                    }
+                }
+                if (has) {
+                    rec[0] = tmin;
+                    rec[1] = dmax;
+                }
+            } else {
+                Transfer<TT> tr;
+                bool zamo = false;
+                if (has) zamo = setup_sample<TT>(p, q, li, tr);
+                c_zamo += __popcll(__ballot(zamo));
+                const unsigned share = 64u / (unsigned)n_want;
+                const unsigned per = NNU == 1 ? 1u : share < (unsigned)p.n_nu ? share : (unsigned)p.n_nu;
+                unsigned is = lane, c = 0;
+                int nu_base = li.nu_base, f = 0, f1 = 1;
+                if (NNU > 1) {
+                    double w[Transfer<TT>::WORDS];
+                    if (has) {
+                        tr.to_words(w);
+#pragma unroll
+                        for (int k = 0; k < Transfer<TT>::WORDS; ++k) rec[k] = w[k];
+                    }
+                    wave_lds_sync();
+                    const unsigned mul = (65535u + per) / per;   // x / per = (x mul) >> 16 for x < 1024
+                    is = (unsigned)lane * mul >> 16;
+                    c = (unsigned)lane - is * per;
+                    rec = ring + (is < (unsigned)n_want ? is : 0u) * REC;
+#pragma unroll
+                    for (int k = 0; k < Transfer<TT>::WORDS; ++k) w[k] = rec[k];
+                    tr.from_words(w);
+                    const int o = link_of(rec)[0];
+                    row = rows + o * ROW;
+                    nu_base = p.jobs[lane_job[o]].nu_base;
+                    const int m = (int)(((unsigned)p.n_nu + per - 1u) * mul >> 16);
+                    f = (int)c * m;
+                    f1 = f + m < p.n_nu ? f + m : p.n_nu;
+                }
+                if (is < (unsigned)n_want) {
+                    if (NNU > 1) {
+                        for (; f + G <= f1; f += G) {
+                            double nu[G], A[G], dt[G], t0[G];
+                            TT att[G];   // formed before the contributions, so that the chains overlap
+#pragma unroll
+                            for (int g = 0; g < G; ++g) {
+                                nu[g] = p.nu[nu_base + f + g];
+                                A[g] = 0.0;
+                                dt[g] = 0.0;
+                                t0[g] = row[COLS + f + g];
+                                att[g] = attenuation<TT>(t0[g]);
+                            }
+                            tr.template contributions<G>(p, nu, G, A, dt);
+#pragma unroll
+                            for (int g = 0; g < G; ++g) fold(f + g, t0[g], att[g], A[g], dt[g]);
+                        }
+                    }
+                    for (; f < f1; ++f) {   // the rest one at a time
+                        double A = 0.0, dt = 0.0;
+                        const double nu1 = p.nu[nu_base + f], t0 = row[COLS + f];
+                        tr.template contributions<1, NNU == 1>(p, &nu1, 1, &A, &dt);
+                        fold(f, t0, attenuation<TT>(t0), A, dt);
+                    }
+                }
+                // over the sample's lanes onto its first, which leaves them in the record
+                for (unsigned off = 1; off < per; off <<= 1) {
+                    const double tm = __shfl_down(tmin, off, 64), dm = __shfl_down(dmax, off, 64);
+                    if (c + off < per) {
+                        tmin = ::fmin(tmin, tm);
+                        dmax = ::fmax(dmax, dm);
+                    }
+                }
+                wave_lds_sync();
+                if (is < (unsigned)n_want && c == 0) {
+                    rec[0] = tmin;
+                    rec[1] = dmax;
+                }
+            }
+            wave_lds_sync();
+            c_samples += n_want;
+            if (__builtin_amdgcn_inverse_ballot_w64(adds)) {
+                row_of(lane)[RATE] = my_rec[1] / my_rec[F_DL];
+                if (p.tau_cutoff > 0.0 && my_rec[0] >= p.tau_cutoff) status = RAY_OPAQUE;
+            }
+            const unsigned long long ended = __ballot(status > RAY_RUNNING) & run;
+            run &= ~ended;
+            wait |= ended;
+            wave_lds_sync();
+        }
+
+        // ------------------------------------------------------------ evaluate queued samples
+        bool round = EACH ? adds != 0ull : total >= 64 || total + n_want > SLOTS;
+        if (!EACH && !round && total > 0)
             round = __popcll(wait) >= __popcll(run) ||
                     (p.tau_cutoff > 0.0 && __ballot(pending() >= CUT_PENDING) != 0ull);
-        if (round) {
+        if (!EACH && round) {
             const TraceParams& p = fresh_params();
             const int lane = fresh(threadIdx.x & 63);
             double* my_row = row_of(lane);
@@ -750,10 +929,9 @@ trace_kernel(TraceParams args)
             const int n_rays = __popcll(rays);
             // Each ray folds its evaluated samples in order, I += exp(-tau) A, tau += dtau: one lane
             // per ray takes all frequencies of a group, or, when there are lanes for it, one lane per
-            // (ray, frequency).  The cut-off and the optical-depth-aware step look at every frequency
-            // of a sample, so their rays fold in one lane.
-            const bool one_lane = p.tau_cutoff > 0.0 || p.tau_step > 0.0;
-            const bool spread = NNU > 1 && n_rays * G <= 64 && !one_lane;
+            // (ray, frequency).  The cut-off looks at every frequency of a sample, so its rays fold in
+            // one lane.
+            const bool spread = NNU > 1 && n_rays * G <= 64 && !(p.tau_cutoff > 0.0);
             if (spread && mine) ray_tab[lane_rank(rays)] = (unsigned char)lane;
             int stop = -1;                 // cut-off: slot of the sample that made the ray opaque
             int nxt = first(), taken = 0;  // after the walk: the ray's oldest sample left and the number folded
@@ -765,7 +943,7 @@ trace_kernel(TraceParams args)
             const bool groups = NNU > FREQ_GROUP && p.tau_cutoff > 0.0 && p.n_nu > G;
             bool probe = groups, question = mine;
             int stop_n = 0;
-            for (int k = 0, f0 = groups && p.tau_step == 0.0 ? lead : 0; k < p.n_nu;) {
+            for (int k = 0, f0 = groups ? lead : 0; k < p.n_nu;) {
                 const int cnt = p.n_nu - f0;
                 double A[G], dt[G];
                 int group_fb = 0, group_dr = 0;
@@ -843,7 +1021,7 @@ trace_kernel(TraceParams args)
                         if (none) lead = f0;
                         probe = !none && k + G < p.n_nu;
                         k = probe ? k + G : 0;
-                        f0 = probe ? (f0 + G < p.n_nu ? f0 + G : 0) : p.tau_step > 0.0 ? 0 : lead;
+                        f0 = probe ? (f0 + G < p.n_nu ? f0 + G : 0) : lead;
                         continue;
                     }
                 }
@@ -911,12 +1089,6 @@ trace_kernel(TraceParams args)
                             }
                         }
                     }
-                    if (p.tau_step > 0.0 && mine) {   // one sample per ray and round
-                        double d1 = f0 == 0 ? 0.0 : my_row[RATE];
-#pragma unroll
-                        for (int g = 0; g < G; ++g) d1 = ::fmax(d1, ring[first() * REC + G + g]);
-                        my_row[RATE] = f0 + G < p.n_nu ? d1 : d1 / ring[first() * REC + F_DL];
-                    }
 #pragma unroll
                     for (int g = 0; g < G; ++g) {
                         if (mine && g < cnt) {
@@ -978,32 +1150,23 @@ trace_kernel(TraceParams args)
         }
 
         // ------------------------------------------------------------ queue this step's samples
-        if (__builtin_amdgcn_inverse_ballot_w64(adds)) {
+        if (!EACH && __builtin_amdgcn_inverse_ballot_w64(adds)) {
             const int lane = fresh(threadIdx.x & 63);
             int s = head + total + (int)lane_rank(adds);
             s = s >= SLOTS ? s - SLOTS : s;
             double* rec = ring + s * REC;
-            rec[0] = y[0];
-            rec[1] = y[1];
-            rec[2] = y[2];
-            rec[3] = y[3];
-            rec[4] = y[4];
-            rec[5] = y[5];
-            rec[6] = y[7];
-            rec[7] = sth;
-            rec[8] = cth;
-            rec[F_DL] = row_of(lane)[RATE];
-            unsigned char* l = link_of(ring, s);
-            *reinterpret_cast<int*>(l) = lane | (int)(queued >> 8 & 0xff0000u);
-            *reinterpret_cast<int*>(l + REC_STEP - REC_LINK) = steps;
+            put(rec, lane);
+            *reinterpret_cast<int*>(link_of(rec) + REC_STEP - REC_LINK) = steps;
             if (pending() > 0)
                 link_of(ring, (int)((queued >> 8) & 255u))[1] = (unsigned char)s;
             else
                 queued = (queued & 0xff000000u) | (unsigned)s;
             queued = ((queued + 0x10000u) & ~0xff00u) | ((unsigned)s << 8);
         }
-        total += __popcll(adds);
-        wave_lds_sync();
+        if (!EACH) {
+            total += __popcll(adds);
+            wave_lds_sync();
+        }
 
         // ------------------------------------------------------------ finished rays
         if (wait != 0ull && (events != 0ull || round)) {
@@ -1092,42 +1255,46 @@ __global__ void reset_kernel(unsigned long long* ray_counter, unsigned long long
 }
 
 // Instantiations: RK4 with every register budget (1, 2 or 3 waves per SIMD), the learned
-// closure with 1 or 2, the second-order integrators with 2 or 3.
+// closure with 1 or 2, the second-order integrators with 2 or 3; all with the sample ring and with the
+// optical-depth-aware step (EACH), whose RK4 kernels hold their registers at 2 waves per SIMD without
+// scratch (at 3, tau_step = 0.1, FP32 transfer, ms at 2 and 3: 512^2, one frequency 6.56 6.66, four
+// 7.94 8.46; 256^2, 24 frequencies 104.4 107.4).
 }  // namespace
 
-int kernel_wpe(int wpe, bool mlpc, int integ)
+int kernel_wpe(int wpe, bool mlpc, int integ, bool each)
 {
     if (integ != INTEG_RK4) return wpe >= 3 ? 3 : 2;   // RK2 and Verlet: two or three waves per SIMD
-    if (mlpc) return wpe >= 2 ? 2 : 1;
+    if (mlpc || each) return wpe >= 2 ? 2 : 1;
     return wpe >= 3 ? 3 : wpe == 2 ? 2 : 1;
 }
 
 namespace {
 
-template <int NNU, class TT>
+template <int NNU, class TT, bool EACH>
 const void* symbol_of(int wpe, bool mlpc, int integ)
 {
-    const int w = kernel_wpe(wpe, mlpc, integ);
+    const int w = kernel_wpe(wpe, mlpc, integ, EACH);
     if (integ == INTEG_RK2)
-        return w == 3 ? (const void*)trace_kernel<NNU, TT, 3, false, INTEG_RK2>
-                      : (const void*)trace_kernel<NNU, TT, 2, false, INTEG_RK2>;
+        return w == 3 ? (const void*)trace_kernel<NNU, TT, 3, false, INTEG_RK2, EACH>
+                      : (const void*)trace_kernel<NNU, TT, 2, false, INTEG_RK2, EACH>;
     if (integ == INTEG_VERLET || integ == INTEG_VERLET_CORR)
-        return w == 3 ? (const void*)trace_kernel<NNU, TT, 3, false, INTEG_VERLET>
-                      : (const void*)trace_kernel<NNU, TT, 2, false, INTEG_VERLET>;
+        return w == 3 ? (const void*)trace_kernel<NNU, TT, 3, false, INTEG_VERLET, EACH>
+                      : (const void*)trace_kernel<NNU, TT, 2, false, INTEG_VERLET, EACH>;
     if (mlpc)
-        return w == 2 ? (const void*)trace_kernel<NNU, TT, 2, true, INTEG_RK4>
-                      : (const void*)trace_kernel<NNU, TT, 1, true, INTEG_RK4>;
-    return w == 3 ? (const void*)trace_kernel<NNU, TT, 3, false, INTEG_RK4>
-         : w == 2 ? (const void*)trace_kernel<NNU, TT, 2, false, INTEG_RK4>
-                  : (const void*)trace_kernel<NNU, TT, 1, false, INTEG_RK4>;
+        return w == 2 ? (const void*)trace_kernel<NNU, TT, 2, true, INTEG_RK4, EACH>
+                      : (const void*)trace_kernel<NNU, TT, 1, true, INTEG_RK4, EACH>;
+    if constexpr (!EACH)
+        if (w == 3) return (const void*)trace_kernel<NNU, TT, 3, false, INTEG_RK4, false>;
+    return w == 2 ? (const void*)trace_kernel<NNU, TT, 2, false, INTEG_RK4, EACH>
+                  : (const void*)trace_kernel<NNU, TT, 1, false, INTEG_RK4, EACH>;
 }
 
-template <class TT>
+template <class TT, bool EACH>
 const void* symbol_tt(int max_nu, int wpe, bool mlpc, int integ)
 {
-    if (max_nu <= 1) return symbol_of<1, TT>(wpe, mlpc, integ);
-    if (max_nu <= 4) return symbol_of<4, TT>(wpe, mlpc, integ);
-    return symbol_of<32, TT>(wpe, mlpc, integ);
+    if (max_nu <= 1) return symbol_of<1, TT, EACH>(wpe, mlpc, integ);
+    if (max_nu <= 4) return symbol_of<4, TT, EACH>(wpe, mlpc, integ);
+    return symbol_of<32, TT, EACH>(wpe, mlpc, integ);
 }
 
 }  // namespace
@@ -1141,11 +1308,12 @@ hipError_t launch_reset(unsigned long long* ray_counter, unsigned long long firs
 
 hipError_t launch_trace(const TraceParams& p, int max_nu, bool fp32, int wpe, int blocks, int threads, hipStream_t st)
 {
-    const void* fn = trace_kernel_symbol(max_nu, fp32, wpe, p.closure >= CL_MLP, p.integrator);
+    const bool each = p.tau_step > 0.0;
+    const void* fn = trace_kernel_symbol(max_nu, fp32, wpe, p.closure >= CL_MLP, p.integrator, each);
     void* args[] = {const_cast<TraceParams*>(&p)};
     return hipLaunchKernel(fn, dim3(blocks), dim3(threads), args,
                            trace_kernel_lds(p.n_nu, wpe, threads, p.closure >= CL_MLP, p.integrator,
-                                            p.rays_per_wave),
+                                            p.rays_per_wave, each),
                            st);
 }
 
@@ -1168,7 +1336,7 @@ hipError_t launch_flux(const DevJob* jobs, int n_jobs, const double* out, const 
 template <class F>
 auto with_queue(int n_nu, int wpe, bool mlpc, int integ, F f)
 {
-    const int w = kernel_wpe(wpe, mlpc, integ);
+    const int w = kernel_wpe(wpe, mlpc, integ, false);   // with EACH any does: the slots are given
     auto per_w = [&](auto m, auto w) {
         constexpr bool M = decltype(m)::value;
         constexpr int W = decltype(w)::value;
@@ -1185,25 +1353,28 @@ auto with_queue(int n_nu, int wpe, bool mlpc, int integ, F f)
 
 bool trace_plan_takes_rays(int max_nu, int wpe, bool mlpc, int integ)
 {
-    return !mlpc && (max_nu > 4 || (max_nu > 1 && kernel_wpe(wpe, mlpc, integ) == 3));
+    return !mlpc && (max_nu > 4 || (max_nu > 1 && kernel_wpe(wpe, mlpc, integ, false) == 3));
 }
 
-int trace_kernel_slots(int n_nu, int wpe, bool mlpc, int integ, int rays)
+int trace_kernel_slots(int n_nu, int wpe, bool mlpc, int integ, int rays, bool each)
 {
+    if (each) return rays;   // one sample per ray
     return with_queue(n_nu, wpe, mlpc, integ, [&](auto q) { return decltype(q)::slots(rays, n_nu); });
 }
 
-size_t trace_kernel_lds(int n_nu, int wpe, int threads, bool mlpc, int integ, int rays)
+size_t trace_kernel_lds(int n_nu, int wpe, int threads, bool mlpc, int integ, int rays, bool each)
 {
-    const size_t per_wave = with_queue(n_nu, wpe, mlpc, integ, [&](auto q) {
-        return decltype(q)::per_wave(rays, decltype(q)::slots(rays, n_nu), n_nu);
-    });
+    const int slots = trace_kernel_slots(n_nu, wpe, mlpc, integ, rays, each);
+    const size_t per_wave =
+        with_queue(n_nu, wpe, mlpc, integ, [&](auto q) { return decltype(q)::per_wave(rays, slots, n_nu); });
     return (size_t)(threads / 64) * per_wave + (mlpc ? (size_t)mlp::LDS_NET_BYTES : 0);
 }
 
-const void* trace_kernel_symbol(int max_nu, bool fp32, int wpe, bool mlpc, int integ)
+const void* trace_kernel_symbol(int max_nu, bool fp32, int wpe, bool mlpc, int integ, bool each)
 {
-    return fp32 ? symbol_tt<float>(max_nu, wpe, mlpc, integ) : symbol_tt<double>(max_nu, wpe, mlpc, integ);
+    if (each)
+        return fp32 ? symbol_tt<float, true>(max_nu, wpe, mlpc, integ) : symbol_tt<double, true>(max_nu, wpe, mlpc, integ);
+    return fp32 ? symbol_tt<float, false>(max_nu, wpe, mlpc, integ) : symbol_tt<double, false>(max_nu, wpe, mlpc, integ);
 }
 
 hipError_t trace_kernel_attributes(int max_nu, bool fp32, int wpe, bool mlpc, int integ, int* vgprs,
