@@ -247,23 +247,24 @@ typedef struct {
     int32_t min_waves_per_simd;  /* 1, 2 or 3: the kernel variant compiled for at least that many
                                     waves per SIMD (register cap 512, 256 or 168); the 3-wave
                                     variant sizes its LDS sample ring for 12 waves per CU */
-    int32_t rays_per_wave;       /* 0 or 64 (default): 64, or fewer in a launch that is too small to
-                                    fill the chip with 64-ray waves, or whose many frequencies per ray
-                                    fill the LDS (the launch chooses; the lanes without a ray then only
-                                    take part in the sample rounds).  32 or 16: that many, for launches
-                                    of several frequencies with the exact or paper closure (more than
-                                    four, or two to four in the 3-wave variant); elsewhere, and as
-                                    installed, 64.  A tile wider than the rays is narrowed to them */
+    int32_t rays_per_wave;       /* 0 (default): the launch chooses, 64 or fewer where it is too small
+                                    to fill the chip with 64-ray waves or where many frequencies per
+                                    ray fill the LDS (the lanes without a ray then only take part in
+                                    the sample rounds).  64, 32 or 16: that many; 32 and 16 for
+                                    launches of several frequencies with the exact or paper closure
+                                    (more than four, or two to four in the 3-wave variant), elsewhere
+                                    they are installed as 64.  A tile wider than the rays is narrowed
+                                    to them */
     int32_t reserved[2];
 } raptor_plan;
 
 /* Current plan for (n_nu, transfer_prec, closure) (the default plan if none was set or tuned:
  * 256 threads, as many work-groups as fit, refill once a wave's rays are all done (64), 8-pixel
- * tile rows, and the
- * variant with the most waves per SIMD (3, 2, then 1) whose RK4 kernel keeps its registers
- * without spilling to scratch; for the learned closures 512 threads and the 2-waves-per-SIMD
- * variant).  RK2 and Verlet runs take the plan's 2- or 3-waves-per-SIMD kernel (2 when the plan
- * asks for 1). */
+ * tile rows, rays per wave chosen by the launch, and the variant with the most waves per SIMD (3,
+ * 2, then 1) whose RK4 kernel keeps its registers without spilling to scratch; for the learned
+ * closures 512 threads and the 2-waves-per-SIMD variant).  RK2 and Verlet runs take the plan's
+ * 2- or 3-waves-per-SIMD kernel (2 when the plan asks for 1), RK4 runs with the optical-depth-aware
+ * step the 1- or 2-wave one. */
 raptor_status raptor_get_plan(raptor_ctx* ctx, int32_t n_nu, int32_t transfer_prec, int32_t closure,
                               raptor_plan* out);
 /* Install a plan for (n_nu, transfer_prec, closure); RAPTOR_E_INVALID if a field is out of range,
@@ -350,7 +351,7 @@ raptor_status raptor_mlp_closure(raptor_ctx* ctx, int32_t form, const float* raw
 
 /* Resources of the trace-kernel instantiation a plan selects: registers per lane, scratch
  * (spill) bytes per lane and resident work-groups per compute unit at the plan's work-group
- * size.  Any output pointer may be NULL. */
+ * size and rays per wave (with 0, at the most that a launch chooses for n_nu).  Any output pointer may be NULL. */
 raptor_status raptor_kernel_info(raptor_ctx* ctx, int32_t n_nu, int32_t transfer_prec, int32_t closure,
                                  const raptor_plan* plan, int32_t* vgprs, int32_t* scratch_bytes,
                                  int32_t* blocks_per_cu);

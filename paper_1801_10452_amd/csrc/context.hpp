@@ -66,7 +66,7 @@ struct NoAllocHost {
 };
 
 struct LaunchPlan {
-    raptor_plan p{256, 0, 64, 8, 2, 64, {0, 0}};
+    raptor_plan p{256, 0, 64, 8, 2, 0, {0, 0}};
     int resident = 1;   // work-groups that a compute unit's registers and wave slots hold at once
 };
 

@@ -165,15 +165,13 @@ struct Geometry {
     int rays, tile_w;
 };
 
-// As the plan asks: fewer than 64 rays only in the classes that take them (raptor_plan), and a tile
-// no wider than the rays.
+// As the plan asks (rays = 0: the launch chooses): fewer than 64 rays only in the classes that take
+// them (raptor_plan), and a tile no wider than the rays.
 Geometry plan_geometry(const raptor_plan& p, int n_nu, bool mlpc, int integ)
 {
-    Geometry g{64, p.tile_width};
-    if ((p.rays_per_wave == 16 || p.rays_per_wave == 32) &&
-        trace_plan_takes_rays(n_nu, p.min_waves_per_simd, mlpc, integ))
-        g.rays = p.rays_per_wave;
-    if (g.tile_w > g.rays) g.tile_w = g.rays;
+    Geometry g{p.rays_per_wave, p.tile_width};
+    if (g.rays != 0 && g.rays != 64 && !trace_plan_takes_rays(n_nu, p.min_waves_per_simd, mlpc, integ)) g.rays = 64;
+    if (g.rays != 0 && g.tile_w > g.rays) g.tile_w = g.rays;
     return g;
 }
 
@@ -189,8 +187,8 @@ int most_rays(int n_nu, bool mlpc, bool cutoff)
     return n_nu > 27 || (n_nu > 16 && !cutoff) ? 16 : n_nu > 8 ? 32 : 64;
 }
 
-// As the launch runs it: a plan with 64 rays per wave lets the launch take fewer where waves would
-// be short.  A wave's iteration costs the same whatever the number of its rays, so few rays per wave
+// As the launch runs it: 64 rays per wave, or, if the plan leaves the choice to the launch, fewer where
+// waves would be short.  A wave's iteration costs the same whatever the number of its rays, so few rays per wave
 // waste the vector lanes of the step; but a launch is no faster than its longest ray, whose wave
 // shares every iteration with the sample rounds of its other rays, and with few rays in all the
 // chip's SIMDs stand idle.  Measured (a = 0.9375, i = 60 deg, ms at 64 / 32 / 16 / 8 / 4 rays, one
@@ -207,7 +205,8 @@ Geometry launch_geometry(const raptor_ctx* ctx, const raptor_plan& p, int n_nu, 
                          const JobIn* in, int nj)
 {
     Geometry g = plan_geometry(p, n_nu, mlpc, o->integrator);
-    if (g.rays < 64) return g;
+    if (g.rays != 0) return g;
+    g.rays = 64;
     long long n = 0;
     for (int k = 0; k < nj; ++k) n += (long long)in[k].cam->nx * in[k].cam->ny;
     const long long simds = 4ll * ctx->cu_count;
@@ -279,8 +278,7 @@ raptor_status resolve_plan(raptor_ctx* ctx, int max_nu, bool fp32, LaunchPlan* p
                                       &max_threads),
               "reading kernel attributes");
     while (pl->p.threads > 64 && pl->p.threads > max_threads) pl->p.threads /= 2;
-    // rays per wave and tile width as the RK4 instantiation runs them (64 rays where it keeps
-    // more than one sample per lane)
+    // rays per wave and tile width as the class takes them
     const Geometry g = plan_geometry(pl->p, max_nu, mlpc, INTEG_RK4);
     pl->p.rays_per_wave = g.rays;
     pl->p.tile_width = g.tile_w;
@@ -292,7 +290,7 @@ raptor_status resolve_plan(raptor_ctx* ctx, int max_nu, bool fp32, LaunchPlan* p
         size_t most = 0;
         for (int n = lo; n <= hi; ++n)
             most = std::max(most, trace_kernel_lds(n, pl->p.min_waves_per_simd, pl->p.threads, mlpc, INTEG_RK4,
-                                                   g.rays == 64 ? most_rays(n, mlpc, true) : g.rays));
+                                                   g.rays ? g.rays : most_rays(n, mlpc, true)));
         return most;
     };
     while (pl->p.threads > 64 && lds() > ctx->lds_per_block) pl->p.threads /= 2;
@@ -1107,7 +1105,8 @@ raptor_status raptor_autotune_batch(raptor_ctx* ctx, const raptor_camera* cams, 
     if ((s = time_plan(bp, &bms)) != RAPTOR_OK) return s;
     // coordinate descent over the plan fields
     // (rays per wave before the tile width, which it bounds)
-    const std::vector<std::vector<int>> values = {{1, 2, 3}, {64, 256, 512}, {0, 2, 4}, {1, 8, 64}, {64, 32, 16},
+    const std::vector<std::vector<int>> values = {{1, 2, 3}, {64, 256, 512}, {0, 2, 4}, {1, 8, 64},
+                                                  {0, 64, 32, 16},
                                                   {8, 16, 64}};
     const bool mlpc_c = o.closure >= RAPTOR_CLOSURE_MLP;
     for (int field = 0; field < (int)values.size(); ++field) {
@@ -1117,8 +1116,8 @@ raptor_status raptor_autotune_batch(raptor_ctx* ctx, const raptor_camera* cams, 
                       : field == 3 ? &c.refill_threshold : field == 4 ? &c.rays_per_wave : &c.tile_width;
             if (*slot == v) continue;
             *slot = v;
-            // rays per wave below 64 only where the instantiation keeps one sample per lane, and
-            // no tile wider than the rays (it would run as the narrower one already timed)
+            // rays per wave only as the class takes them, and no tile wider than the rays (it would run
+            // as the narrower one already timed)
             const Geometry cg = plan_geometry(c, n_nu, mlpc_c, o.integrator);
             if (field == 4 && cg.rays != v) continue;
             if (field == 5 && cg.tile_w != v) continue;
@@ -1156,11 +1155,12 @@ raptor_status raptor_kernel_info(raptor_ctx* ctx, int32_t n_nu, int32_t transfer
     int regs = 0, spill = 0, maxt = 0, per_cu = 0;
     RAPTOR_CK(trace_kernel_attributes(n_nu, fp32, plan->min_waves_per_simd, mlpc, INTEG_RK4, &regs, &spill, &maxt),
               "reading kernel attributes");
+    // (for a plan that leaves the rays to the launch: the most that one takes)
+    const Geometry g = plan_geometry(*plan, n_nu, mlpc, INTEG_RK4);
     RAPTOR_CK(hipOccupancyMaxActiveBlocksPerMultiprocessor(
                   &per_cu, trace_kernel_symbol(n_nu, fp32, plan->min_waves_per_simd, mlpc), plan->threads,
                   trace_kernel_lds(n_nu, plan->min_waves_per_simd, plan->threads, mlpc, INTEG_RK4,
-                                   std::min(plan_geometry(*plan, n_nu, mlpc, INTEG_RK4).rays,
-                                            most_rays(n_nu, mlpc, false)))),
+                                   g.rays ? g.rays : most_rays(n_nu, mlpc, false))),
               "querying occupancy");
     if (vgprs) *vgprs = regs;
     if (scratch_bytes) *scratch_bytes = spill;

@@ -403,8 +403,8 @@ def trace_batch_noalloc(ctx, cams, grids, nu, opts, images, flux=None):
     return st
 
 
-def make_plan(threads=256, blocks_per_cu=0, refill_threshold=1, tile_width=8, min_waves_per_simd=2,
-              rays_per_wave=64) -> CPlan:
+def make_plan(threads=256, blocks_per_cu=0, refill_threshold=64, tile_width=8, min_waves_per_simd=2,
+              rays_per_wave=0) -> CPlan:
     return CPlan(threads, blocks_per_cu, refill_threshold, tile_width, min_waves_per_simd, rays_per_wave,
                  (C.c_int32 * 2)())
 
