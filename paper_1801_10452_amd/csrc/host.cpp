@@ -195,21 +195,39 @@ int most_rays(int n_nu, bool mlpc, bool cutoff)
 // frequency, FP32 transfer): 64^2 2.96 2.61 2.24 2.12 2.06; 96^2 2.69 2.12 1.98 1.86 1.92; 150^2
 // 2.98 2.30 2.00 2.14 3.21; 230^2 4.10 3.49 3.62 4.25 5.40; 400^2 (FP64) 4.48 3.85 4.77 7.69; 480^2
 // 4.67 4.73 6.18; 700^2 7.00 7.66; with the rounds evened (launch_blocks) 256^2 3.57 3.20 3.10 4.38, 512 x
-// 256 4.35 3.90 4.68 7.58.  Between one and a half and two rounds of 64-ray tiles the last
-// round is mostly empty: 512^2 (1.33 rounds) 5.59 4.89 6.77.  More than four frequencies and the
-// learned closure have heavier rounds, and their lines for 4, 8 and 16 rays lie at twice the rays (24
-// frequencies, 256^2: 9.98 7.81 5.38 5.76 8.29; but 6 frequencies, 2 x 480 x 400: 9.69 10.7 13.2), the
-// learned closure's for 32 too (200^2: 9.11 5.80 3.76 4.79 5.70), at four times for both together (4
-// frequencies, 4 x 256^2: 40.1 33.0 29.5 34.1).
+// 256 4.35 3.90 4.68 7.58.  More than four frequencies and the learned closure have heavier rounds, and
+// their lines for 4, 8 and 16 rays lie at twice the rays (24 frequencies, 256^2: 9.98 7.81 5.38 5.76 8.29;
+// but 6 frequencies, 2 x 480 x 400: 9.69 10.7 13.2), the learned closure's for 32 too (200^2: 9.11 5.80 3.76
+// 4.79 5.70), at four times for both together (4 frequencies, 4 x 256^2: 40.1 33.0 29.5 34.1).
+//
+// Images below 144^2 hold no rays as long as a large one's (the longest come from next to the photon ring,
+// and pixels meet it the closer the finer they are), so a launch of many is bound by its lanes much
+// earlier: its lines for 16 and 32 rays lie at fewer rays, by the images' side, up to a third (64 / 32 / 16
+// rays: 100 of 32 x 31, five frequencies 3.59 3.41 5.66, with the cut-off 3.94 4.02 6.87; 24 of 64 x 40, one
+// frequency 2.02 2.05 3.16, five 3.06 2.80 3.72; 141 of 32 x 31 2.93 4.30 6.10), and to two thirds for 32 rays
+// (99 of 32 x 31 at four frequencies, Verlet 2.31 2.08 3.30).
+//
+// Above the last line a lone image keeps 32 rays a little longer where its rounds are heavy: its longest
+// rays lie in one band of tiles (ms at 64 and 32 rays, FP64 transfer: 512^2 5.62 5.40, 520 x 512 5.83
+// 5.48, 504 x 520 5.73 5.31, but 540^2 5.23 6.00, 580^2 5.85 6.36, and 470^2 5.29 5.55; four frequencies 512^2
+// 8.26 7.06, 540^2 7.50 7.85; RK2, one frequency 496^2 4.75 4.25, 540^2 5.24 4.63, 580^2 5.02 5.51; eight
+// frequencies 496^2 11.2 11.0, 540^2 12.3 10.4, 580^2 13.7 12.4, 600 x 380 11.5 9.9).  Not with one frequency
+// whose rounds are light (FP32: 496^2 4.96 5.37, 512 x 500 4.68 5.35, 512^2 5.14 5.00, 540^2 4.72 5.75; FP64
+// with the cut-off: 512^2 4.00 4.90), nor several images, whose longest rays lie apart (four of 256^2
+// 5.10 5.53, 16 of 128^2 4.86 5.42, 70 of 64^2 5.34 6.45).
 Geometry launch_geometry(const raptor_ctx* ctx, const raptor_plan& p, int n_nu, bool mlpc, const raptor_opts* o,
                          const JobIn* in, int nj)
 {
     Geometry g = plan_geometry(p, n_nu, mlpc, o->integrator);
     if (g.rays != 0) return g;
     g.rays = 64;
-    long long n = 0;
-    for (int k = 0; k < nj; ++k) n += (long long)in[k].cam->nx * in[k].cam->ny;
-    const long long simds = 4ll * ctx->cu_count;
+    double n = 0.0, largest = 0.0;
+    for (int k = 0; k < nj; ++k) {
+        const double rays = (double)in[k].cam->nx * in[k].cam->ny;
+        n += rays;
+        largest = std::max(largest, rays);
+    }
+    const double simds = 4.0 * ctx->cu_count;
     // The optical-depth-aware step has a round at every step, whose samples share the wave's lanes by
     // frequency.  With many frequencies 32 rays leave fewer lanes idle, and take half the LDS; with few
     // the lanes of the step itself count (ms at 64 and 32 rays, FP32 and FP64 transfer: four frequencies
@@ -221,15 +239,19 @@ Geometry launch_geometry(const raptor_ctx* ctx, const raptor_plan& p, int n_nu, 
         if (g.tile_w > g.rays) g.tile_w = g.rays;
         return g;
     }
-    const long long few = n / (mlpc && n_nu > 1 ? 4 : mlpc || n_nu > 4 ? 2 : 1);
-    if (mlpc) n = few;
-    g.rays = few <= simds * 6     ? 4     // up to 1.5 tiles of the size per SIMD
-           : few <= simds * 12    ? 8     // 1.5
-           : few <= simds * 64    ? 16    // 4
-           : n <= simds * 192     ? 32    // 6 (the resident 64-ray tiles)
-           : n > simds * 240 && n < simds * 336 ? 32
-                                  : 64;
-    g.rays = std::min(g.rays, most_rays(n_nu, mlpc, o->tau_cutoff > 0.0));
+    const bool cut = o->tau_cutoff > 0.0, second = o->integrator != INTEG_RK4;
+    const double few = n / (mlpc && n_nu > 1 ? 4 : mlpc || n_nu > 4 ? 2 : 1);
+    const double small =
+        mlpc && n_nu > 1 ? 1.0 : std::min(3.0, std::max(1.0, 144.0 / std::sqrt(largest)));
+    const bool heavy = n_nu > 1 || second || (o->transfer_prec == RAPTOR_F64 && !cut);
+    const bool lone = !mlpc && 2.0 * largest > n &&
+                      (n_nu > 4 ? n < simds * 336 : heavy && n > simds * 240 && n < simds * (second ? 300 : 272));
+    g.rays = few <= simds * 6                                          ? 4    // up to 1.5 tiles of the size per SIMD
+           : few <= simds * 12                                         ? 8    // 1.5
+           : few * small <= simds * 64                                 ? 16   // 4
+           : (mlpc ? few : n) * std::min(1.5, small) <= simds * 192 || lone ? 32   // 6 (the resident 64-ray tiles)
+                                                                       : 64;
+    g.rays = std::min(g.rays, most_rays(n_nu, mlpc, cut));
     if (g.tile_w > g.rays) g.tile_w = g.rays;
     return g;
 }

@@ -1,0 +1,46 @@
+"""The rays per wave that a launch takes by itself, against plans that name them: many small images, whose
+waves run out of lanes long before they run out of tiles, and images around one and a third rounds of
+tiles.  The launch's own choice is no more than 1.15 times as slow as the faster of 64 and 32 rays, and its
+images are theirs bit for bit."""
+import math
+
+import numpy as np
+import pytest
+
+import synthetic as S
+
+pytestmark = pytest.mark.gpu
+
+
+def fastest(R, ctx, cams, gh, nu, opts, plan=None):
+    prec = opts.transfer_prec
+    own = R.get_plan(ctx, len(nu), prec)
+    if plan is not None:
+        own_rays = own.rays_per_wave
+        own.rays_per_wave = plan
+        R.set_plan(ctx, len(nu), prec, own)
+    runs = [ctx.trace_batch(cams, [gh] * len(cams), nu, opts) for _ in range(8)]
+    if plan is not None:
+        own.rays_per_wave = own_rays
+        R.set_plan(ctx, len(nu), prec, own)
+    return min(r[2].kernel_ms for r in runs), runs[-1][0]
+
+
+@pytest.mark.parametrize("nx,ny,images,n_nu,prec,cut", [(32, 31, 100, 5, "F32", True), (32, 31, 100, 8, "F64", False),
+                                                        (64, 40, 24, 12, "F32", True), (64, 64, 16, 6, "F32", False),
+                                                        (540, 540, 1, 12, "F32", False), (600, 380, 1, 8, "F64", False)])
+def test_own_choice_is_no_slower(nx, ny, images, n_nu, prec, cut):
+    from paper_1801_10452_amd import raptor as R
+    ctx = R.Context(0)
+    gh = ctx.upload_grid(S.make_grid(128, 128, a_gen=0.9375, dtype=np.float32))
+    cams = [S.Camera(spin=0.9375, incl_deg=60.0, nx=nx, ny=ny)] * images
+    nu = list(np.geomspace(1e9, 7e9, n_nu)) if cut else list(np.geomspace(2e10, 1e12, n_nu))
+    opts = R.default_opts(transfer_prec=getattr(R, prec), tau_cutoff=math.log(1000.0) if cut else 0.0)
+    ms, img = fastest(R, ctx, cams, gh, nu, opts)
+    named = {rays: fastest(R, ctx, cams, gh, nu, opts, rays) for rays in (64, 32)}
+    print(f"[rays per wave] {images} x {nx} x {ny}, {n_nu} frequencies: {ms:.2f} ms, named "
+          f"{ {k: round(v[0], 2) for k, v in named.items()} }", flush=True)
+    for rays, (_, other) in named.items():
+        assert np.array_equal(img, other), rays
+    assert ms <= 1.15 * min(v[0] for v in named.values())
+    ctx.close()
