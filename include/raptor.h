@@ -264,7 +264,7 @@ typedef struct {
  * 2, then 1) whose RK4 kernel keeps its registers without spilling to scratch; for the learned
  * closures 512 threads and the 2-waves-per-SIMD variant).  RK2 and Verlet runs take the plan's
  * 2- or 3-waves-per-SIMD kernel (2 when the plan asks for 1), RK4 runs with the optical-depth-aware
- * step the 1- or 2-wave one. */
+ * step, or with the cut-off and more than 12 frequencies, the 1- or 2-wave one. */
 raptor_status raptor_get_plan(raptor_ctx* ctx, int32_t n_nu, int32_t transfer_prec, int32_t closure,
                               raptor_plan* out);
 /* Install a plan for (n_nu, transfer_prec, closure); RAPTOR_E_INVALID if a field is out of range,

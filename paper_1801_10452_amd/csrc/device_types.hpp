@@ -71,7 +71,8 @@ struct TraceParams {
     int n_nu, slots;                    // frequencies of every job; sample-ring slots of a wave
     double r_in, r_out;                 // radial range of every grid (r_in = r_out = 0: they differ)
     double eps, M, length_unit, const_j, const_alpha, tau_cutoff;
-    double tau_step;           // > 0: optical-depth-aware step (at most tau_step per step at the last sample)
+    double tau_step;           // > 0: each sample right after its step, which takes at most tau_step of the
+                               // last sample's optical depth (infinite: any)
     // learned closure (closure == CL_MLP): FP32 parameters and padded BF16 hi / lo weights
     const float* mlp_P;
     const unsigned short* mlp_W;

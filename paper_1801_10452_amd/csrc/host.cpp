@@ -160,9 +160,11 @@ int log2_of(int v)
     return k;
 }
 
-// Rays per wave and tile width of a launch.
+// Rays per wave and tile width of a launch, and whether its samples are evaluated right after their
+// steps instead of through the ring.
 struct Geometry {
     int rays, tile_w;
+    bool each = false;
 };
 
 // As the plan asks (rays = 0: the launch chooses): fewer than 64 rays only in the classes that take
@@ -215,12 +217,17 @@ int most_rays(int n_nu, bool mlpc, bool cutoff)
 // whose rounds are light (FP32: 496^2 4.96 5.37, 512 x 500 4.68 5.35, 512^2 5.14 5.00, 540^2 4.72 5.75; FP64
 // with the cut-off: 512^2 4.00 4.90), nor several images, whose longest rays lie apart (four of 256^2
 // 5.10 5.53, 16 of 128^2 4.86 5.42, 70 of 64^2 5.34 6.45).
+//
+// The cut-off with more than 12 frequencies runs in the kernels of the optical-depth-aware step, with no
+// limit on the step: the ring's rounds hold few samples of a ray there, look at every group of frequencies
+// before they fold any, and fold in one lane per ray.  The same images bit for bit (ring and each, the better
+// rays: 32 frequencies, FP32, 512^2 19.1 13.6, 24 of 64 x 40 7.6 5.1, FP64 512^2 28 21.7; 24, 230^2 11.0 9.1,
+// 512^2 14.3 12.3; 16, 11.4 11.2; but 12, 9.2 9.8 and 230^2 7.5 8.3).  Constant coefficients, whose
+// evaluation costs nothing, go there without the cut-off too, for more than 16 frequencies and enough rays
+// (32 frequencies, 512^2 12.7 9.7, 24 of 64 x 40 5.1 3.8; but 230^2 6.9 8.0).
 Geometry launch_geometry(const raptor_ctx* ctx, const raptor_plan& p, int n_nu, bool mlpc, const raptor_opts* o,
                          const JobIn* in, int nj)
 {
-    Geometry g = plan_geometry(p, n_nu, mlpc, o->integrator);
-    if (g.rays != 0) return g;
-    g.rays = 64;
     double n = 0.0, largest = 0.0;
     for (int k = 0; k < nj; ++k) {
         const double rays = (double)in[k].cam->nx * in[k].cam->ny;
@@ -228,6 +235,16 @@ Geometry launch_geometry(const raptor_ctx* ctx, const raptor_plan& p, int n_nu, 
         largest = std::max(largest, rays);
     }
     const double simds = 4.0 * ctx->cu_count;
+    const bool cut = o->tau_cutoff > 0.0, second = o->integrator != INTEG_RK4;
+    const double few = n / (mlpc && n_nu > 1 ? 4 : mlpc || n_nu > 4 ? 2 : 1);
+    const double small =
+        mlpc && n_nu > 1 ? 1.0 : std::min(3.0, std::max(1.0, 144.0 / std::sqrt(largest)));
+    Geometry g = plan_geometry(p, n_nu, mlpc, o->integrator);
+    const bool split = !mlpc && n_nu > 12 &&
+                       (cut || (o->closure == RAPTOR_CLOSURE_CONST && n_nu > 16 && n * small > simds * 128));
+    g.each = o->tau_step > 0.0 || split;
+    if (g.rays != 0) return g;
+    g.rays = 64;
     // The optical-depth-aware step has a round at every step, whose samples share the wave's lanes by
     // frequency.  With many frequencies 32 rays leave fewer lanes idle, and take half the LDS; with few
     // the lanes of the step itself count (ms at 64 and 32 rays, FP32 and FP64 transfer: four frequencies
@@ -239,10 +256,14 @@ Geometry launch_geometry(const raptor_ctx* ctx, const raptor_plan& p, int n_nu, 
         if (g.tile_w > g.rays) g.tile_w = g.rays;
         return g;
     }
-    const bool cut = o->tau_cutoff > 0.0, second = o->integrator != INTEG_RK4;
-    const double few = n / (mlpc && n_nu > 1 ? 4 : mlpc || n_nu > 4 ? 2 : 1);
-    const double small =
-        mlpc && n_nu > 1 ? 1.0 : std::min(3.0, std::max(1.0, 144.0 / std::sqrt(largest)));
+    // The same rounds without its short steps (32 / 16 / 8 / 4 rays, 24 frequencies, FP32): 13 x 7 6.8 6.4 6.9
+    // 6.8, 64^2 5.3 4.7 4.5 4.4, 128^2 5.3 4.7 5.0 5.1, 230^2 9.6 9.1 9.5 12.0, 20 of 32 x 31 3.2 3.8 4.7 5.2.
+    if (split) {
+        const double f = few * small / simds;
+        g.rays = f < 4 ? 4 : f < 8 ? 8 : f <= 32 ? 16 : 32;
+        if (g.tile_w > g.rays) g.tile_w = g.rays;
+        return g;
+    }
     const bool heavy = n_nu > 1 || second || (o->transfer_prec == RAPTOR_F64 && !cut);
     const bool lone = !mlpc && 2.0 * largest > n &&
                       (n_nu > 4 ? n < simds * 336 : heavy && n > simds * 240 && n < simds * (second ? 300 : 272));
@@ -524,8 +545,7 @@ raptor_status launch_tables(raptor_ctx* ctx, const HostTables& h, const DevTable
     const bool fp32 = o->transfer_prec == RAPTOR_F32;
     const bool mlpc = o->closure >= RAPTOR_CLOSURE_MLP;
     const int rays_shift = log2_of(geo.rays);
-    const bool each = o->tau_step > 0.0;
-    const int blocks = launch_blocks(ctx, plan, n_nu, mlpc, o->integrator, geo.rays, each, h.tiles);
+    const int blocks = launch_blocks(ctx, plan, n_nu, mlpc, o->integrator, geo.rays, geo.each, h.tiles);
     hipStream_t s = ctx->stream;
     RAPTOR_CK(hipMemcpyAsync(d.jobs, h.jobs, nj * sizeof(DevJob), hipMemcpyHostToDevice, s), "uploading jobs");
     RAPTOR_CK(hipMemcpyAsync(d.grids, h.grids, h.n_grids * sizeof(DevGrid), hipMemcpyHostToDevice, s),
@@ -558,7 +578,7 @@ raptor_status launch_tables(raptor_ctx* ctx, const HostTables& h, const DevTable
     p.const_j = o->const_j;
     p.const_alpha = o->const_alpha;
     p.tau_cutoff = o->tau_cutoff;
-    p.tau_step = o->tau_step;
+    p.tau_step = o->tau_step > 0.0 || !geo.each ? o->tau_step : INFINITY;
     p.mlp_P = ctx->mlp.P.p;
     p.mlp_W = ctx->mlp.W.p;
     p.mlp_Wlo = ctx->mlp.Wlo.p;
@@ -567,7 +587,7 @@ raptor_status launch_tables(raptor_ctx* ctx, const HostTables& h, const DevTable
     p.rays_per_wave = geo.rays;
     p.rays_shift = rays_shift;
     p.n_nu = n_nu;
-    p.slots = trace_kernel_slots(n_nu, plan.p.min_waves_per_simd, mlpc, o->integrator, geo.rays, each);
+    p.slots = trace_kernel_slots(n_nu, plan.p.min_waves_per_simd, mlpc, o->integrator, geo.rays, geo.each);
     p.r_in = h.grids[0].r_in;
     p.r_out = h.grids[0].r_out;
     for (int i = 1; i < h.n_grids; ++i)

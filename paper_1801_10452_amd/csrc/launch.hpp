@@ -20,7 +20,7 @@ hipError_t trace_kernel_attributes(int max_nu, bool fp32, int wpe, bool mlpc, in
                                    int* spill_bytes, int* max_threads);
 // mlpc: the variant with the learned closure; integ: INTEG_* (the second-order integrators have
 // the 2- and 3-waves-per-SIMD variants; a request for 1 takes 2)
-// each: the kernels of the optical-depth-aware step, which evaluate each sample after its step
+// each: the kernels that evaluate each sample after its step (p.tau_step > 0)
 const void* trace_kernel_symbol(int max_nu, bool fp32, int wpe, bool mlpc = false, int integ = INTEG_RK4,
                                 bool each = false);
 // A compute unit's LDS, and the granules it is handed out in.

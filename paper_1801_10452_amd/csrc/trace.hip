@@ -290,7 +290,8 @@ __device__ inline float attenuation<float>(double tau) { return rt::exp_mixed(-t
 // step.  A ray that has ended waits in its lane until its samples are folded.
 //
 // The optical-depth-aware step needs each sample before its ray goes on: its kernels (EACH) queue
-// nothing and evaluate and fold the samples of a step at once, one per ray.
+// nothing and evaluate and fold the samples of a step at once, one per ray.  Launches whose rounds the
+// ring does not fill, or whose folds outweigh them (launch_geometry), run there too.
 //
 // A ring shared by the wave, against a queue of K samples per lane (K = 1 to 3) whose first full
 // lane forced a round: a lone long ray at the end of a wave's work has a round every 64 of its

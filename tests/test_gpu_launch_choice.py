@@ -1,7 +1,8 @@
 """The rays per wave that a launch takes by itself, against plans that name them: many small images, whose
 waves run out of lanes long before they run out of tiles, and images around one and a third rounds of
 tiles.  The launch's own choice is no more than 1.15 times as slow as the faster of 64 and 32 rays, and its
-images are theirs bit for bit."""
+images are theirs bit for bit.  The cut-off with many frequencies against the same call with an
+optical-depth-aware step that limits nothing: no slower, the same images and counters."""
 import math
 
 import numpy as np
@@ -43,4 +44,28 @@ def test_own_choice_is_no_slower(nx, ny, images, n_nu, prec, cut):
     for rays, (_, other) in named.items():
         assert np.array_equal(img, other), rays
     assert ms <= 1.15 * min(v[0] for v in named.values())
+    ctx.close()
+
+
+@pytest.mark.parametrize("nx,ny,images,n_nu,prec,closure,cut", [
+    (64, 40, 24, 32, "F32", "EXACT", True), (32, 31, 20, 16, "F64", "EXACT", True), (13, 7, 1, 13, "F64", "EXACT", True),
+    (230, 230, 1, 24, "F64", "K2_PAPER", True), (64, 40, 24, 17, "F32", "CONST", False),
+    (512, 512, 1, 32, "F32", "CONST", False)])
+def test_cutoff_with_many_frequencies(nx, ny, images, n_nu, prec, closure, cut):
+    from paper_1801_10452_amd import raptor as R
+    ctx = R.Context(0)
+    gh = ctx.upload_grid(S.make_grid(128, 128, a_gen=0.9375, dtype=np.float32))
+    cams = [S.Camera(spin=0.9375, incl_deg=60.0, nx=nx, ny=ny)] * images
+    nu = list(np.geomspace(1e9, 7e9, n_nu))
+    kw = dict(transfer_prec=getattr(R, prec), closure=getattr(R, "CLOSURE_" + closure), const_j=1e-20, const_alpha=1e-14,
+              tau_cutoff=math.log(1000.0) if cut else 0.0)
+    ms, img = fastest(R, ctx, cams, gh, nu, R.default_opts(**kw))
+    each_ms, each = fastest(R, ctx, cams, gh, nu, R.default_opts(tau_step=1e30, **kw))
+    print(f"[many frequencies] {images} x {nx} x {ny}, {n_nu} frequencies, {closure}: {ms:.2f} ms, each sample after its "
+          f"step {each_ms:.2f}", flush=True)
+    assert np.array_equal(img, each)
+    st, st1 = (ctx.trace_batch(cams, [gh] * images, nu, R.default_opts(**k))[2] for k in (kw, dict(kw, tau_step=1e30)))
+    for f in ("rays", "ray_steps", "samples", "n_pole", "n_opaque", "n_zamo_fallback"):
+        assert getattr(st, f) == getattr(st1, f), f
+    assert ms <= 1.15 * each_ms
     ctx.close()
