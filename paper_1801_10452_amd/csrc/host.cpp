@@ -201,6 +201,7 @@ int most_rays(int n_nu, bool mlpc, bool cutoff)
 // their lines for 4, 8 and 16 rays lie at twice the rays (24 frequencies, 256^2: 9.98 7.81 5.38 5.76 8.29;
 // but 6 frequencies, 2 x 480 x 400: 9.69 10.7 13.2), the learned closure's for 32 too (200^2: 9.11 5.80 3.76
 // 4.79 5.70), at four times for both together (4 frequencies, 4 x 256^2: 40.1 33.0 29.5 34.1).
+// (All with the installed plans' three waves per SIMD, the learned closure's two.)
 //
 // Images below 144^2 hold no rays as long as a large one's (the longest come from next to the photon ring,
 // and pixels meet it the closer the finer they are), so a launch of many is bound by its lanes much
@@ -237,8 +238,8 @@ Geometry launch_geometry(const raptor_ctx* ctx, const raptor_plan& p, int n_nu, 
     const double simds = 4.0 * ctx->cu_count;
     const bool cut = o->tau_cutoff > 0.0, second = o->integrator != INTEG_RK4;
     const double few = n / (mlpc && n_nu > 1 ? 4 : mlpc || n_nu > 4 ? 2 : 1);
-    const double small =
-        mlpc && n_nu > 1 ? 1.0 : std::min(3.0, std::max(1.0, 144.0 / std::sqrt(largest)));
+    const double side = std::max(1.0, 144.0 / std::sqrt(largest));
+    const double small = mlpc && n_nu > 1 ? 1.0 : std::min(3.0, side);
     Geometry g = plan_geometry(p, n_nu, mlpc, o->integrator);
     const bool split = !mlpc && n_nu > 12 &&
                        (cut || (o->closure == RAPTOR_CLOSURE_CONST && n_nu > 16 && n * small > simds * 128));
@@ -259,7 +260,7 @@ Geometry launch_geometry(const raptor_ctx* ctx, const raptor_plan& p, int n_nu, 
     // The same rounds without its short steps (32 / 16 / 8 / 4 rays, 24 frequencies, FP32): 13 x 7 6.8 6.4 6.9
     // 6.8, 64^2 5.3 4.7 4.5 4.4, 128^2 5.3 4.7 5.0 5.1, 230^2 9.6 9.1 9.5 12.0, 20 of 32 x 31 3.2 3.8 4.7 5.2.
     if (split) {
-        const double f = few * small / simds;
+        const double f = few * side / simds;
         g.rays = f < 4 ? 4 : f < 8 ? 8 : f <= 32 ? 16 : 32;
         if (g.tile_w > g.rays) g.tile_w = g.rays;
         return g;

@@ -69,3 +69,33 @@ def test_cutoff_with_many_frequencies(nx, ny, images, n_nu, prec, closure, cut):
         assert getattr(st, f) == getattr(st1, f), f
     assert ms <= 1.15 * each_ms
     ctx.close()
+
+
+def test_cutoff_route_in_graphs_and_without_allocation():
+    """The same launch direct, replayed as a graph between other launches, without allocation, and under
+    plans that name 64, 32 and 16 rays and each number of waves: the same images bit for bit."""
+    import torch
+    from paper_1801_10452_amd import raptor as R
+    ctx = R.Context(0)
+    gh = ctx.upload_grid(S.make_grid(64, 64, a_gen=0.9375, dtype=np.float32))
+    cams = [S.Camera(spin=0.9375, incl_deg=60.0, nx=37, ny=21), S.Camera(spin=0.9375, incl_deg=30.0, nx=9, ny=40)]
+    nu = list(np.geomspace(1e9, 7e9, 17))
+    kw = dict(transfer_prec=R.F32, tau_cutoff=math.log(1000.0))
+    ref, ref_flux, st = ctx.trace_batch(cams, [gh] * 2, nu, R.default_opts(**kw))
+    assert st.n_opaque > 0
+    images = torch.empty(ref.size, dtype=torch.float64, device="cuda")
+    flux = torch.empty(2 * 17, dtype=torch.float64, device="cuda")
+    for k in range(3):
+        images.zero_()
+        ctx.trace_batch(cams, [gh] * 2, nu, R.default_opts(mem=R.MEM_DEVICE, launch=R.LAUNCH_GRAPH, **kw), images, flux)
+        assert np.array_equal(images.cpu().numpy(), ref) and np.array_equal(flux.cpu().numpy(), ref_flux.ravel()), k
+        ctx.trace_spectrum(cams[0], gh, nu[:1 + k], R.default_opts(transfer_prec=R.F32))
+    images.zero_()
+    R.trace_batch_noalloc(ctx, cams, [gh] * 2, nu, R.default_opts(mem=R.MEM_DEVICE, **kw), images, flux)
+    assert np.array_equal(images.cpu().numpy(), ref) and np.array_equal(flux.cpu().numpy(), ref_flux.ravel())
+    for rays in (0, 16, 32, 64):
+        for waves in (1, 2, 3):
+            R.set_plan(ctx, 17, R.F32, R.make_plan(rays_per_wave=rays, min_waves_per_simd=waves))
+            got, got_flux, _ = ctx.trace_batch(cams, [gh] * 2, nu, R.default_opts(**kw))
+            assert np.array_equal(got, ref) and np.array_equal(got_flux, ref_flux), (rays, waves)
+    ctx.close()
